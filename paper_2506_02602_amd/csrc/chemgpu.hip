@@ -154,27 +154,40 @@ __global__ void pool_reset(unsigned long long* next, unsigned int* tail_count,
 // longest-processing-time rule of list scheduling) keeps a long cell from
 // starting late, and when the list is resumed one per lane it keeps the
 // launch from draining on long cells claimed last.  A cell's remaining work
-// is estimated from its state at the hand-off, in its current step size:
-// rem/h steps for the time rem left in its flow step (all remaining
-// sub-calls); the key buckets that estimate four to an octave, 0 for fewer
-// than two steps, up to kTailBuckets - 1.
+// is estimated from its state at the hand-off, in its current step size
+// (tail_steps_left); the key buckets that estimate four to an octave, 0 for
+// fewer than two steps, up to kTailBuckets - 1.
 constexpr int kTailBuckets = 64;
 
-__device__ __forceinline__ int32_t tail_key(double rem, double h) {
+// rem/h steps for the time rem left in the present sub-call, and in each of
+// the `later` ones the geometric mean of one step and of the dt/h it would
+// take at the present step size: a cell of a step per sub-call may ignite in a
+// later one, and one that steps finely now is often in a transient.  Rank
+// correlation with the steps that the cells then take (hand-off after 4 steps;
+// the present step size to the end instead): 65,536-cell ignition profiles
+// through 100 sub-calls 0.88 and 0.91 (0.77, 0.78), through 30 0.92 and 0.95
+// (0.81, 0.82), hot cells through 4 0.98 (0.98).
+__device__ __forceinline__ double tail_steps_left(double rem, double dt, int later, double h) {
   const double est = rem / h;
+  return est + (float)later * fmaxf(1.f, __builtin_amdgcn_sqrtf((float)(dt / h)));
+}
+
+__device__ __forceinline__ int32_t tail_key(double est) {
   if (!(est > 1.0)) return 0;
   const double k = 4.0 * log2(est);
   return k >= (double)(kTailBuckets - 1) ? kTailBuckets - 1 : (int32_t)k;
 }
 
-// All the estimated steps of the list and the longest cell's, from the key
-// histogram, a bucket a lane (every lane of the wave calls it).
-__device__ __forceinline__ void tail_estimate(const unsigned int* btot, float& sum, float& top) {
+// All the estimated steps of the list and the longest cell's, each cell's
+// estimate to the power p, from the key histogram, a bucket a lane (every lane
+// of the wave calls it).
+__device__ __forceinline__ void tail_estimate(const unsigned int* btot, float p, float& sum,
+                                              float& top) {
   const int lane = threadIdx.x & 63;
   const unsigned int n = btot[lane];
   const unsigned long long some = __ballot(n != 0u);
-  top = exp2f((float)(some ? 64 - __clzll(some) : 1) * 0.25f);
-  sum = (float)n * exp2f(((float)lane + 0.5f) * 0.25f);
+  top = exp2f((float)(some ? 64 - __clzll(some) : 1) * (0.25f * p));
+  sum = (float)n * exp2f(((float)lane + 0.5f) * (0.25f * p));
 #pragma unroll
   for (int w = 32; w > 0; w >>= 1) sum += __shfl_xor(sum, w);
 }
@@ -190,7 +203,7 @@ __device__ __forceinline__ void tail_estimate(const unsigned int* btot, float& s
 // Scheduling only: no result depends on it.
 __device__ __forceinline__ float resume_priority(const unsigned int* btot, float lanes) {
   float sum, top;
-  tail_estimate(btot, sum, top);
+  tail_estimate(btot, 1.f, sum, top);
   return top >= sum / lanes ? 0.5f * top : 0.f;
 }
 
@@ -199,13 +212,23 @@ __device__ __forceinline__ float resume_priority(const unsigned int* btot, float
 // either ends when its longest cell does, and no sooner than its share of all
 // the estimated steps is done.  In units of a lone cooperative group's step
 // (4.2 us for 9 species, 27 us for 32), a per-lane step of a wave that shares
-// its SIMD takes kLaneStep (3.4 where it has it alone).  Measured (9 species;
-// cooperative against per lane, ms): 40,000 hot cells 1.9, 3.1; 50,000 of a
-// stress field 1.6, 2.8; 65,536 hot cells 3.1, 3.0; 100,000 of a stress field
-// 3.0, 2.8; 130,000 hot cells 5.6, 3.3.  The estimate is poor where a cell's
-// step size changes much on the way (65,536 cells through 100 sub-calls each:
-// 18, 7.5, and it says cooperative), hence a cap on the list (192 cells per
-// CU) beside it.
+// its SIMD takes kLaneStep (3.4 where it has it alone).  The steps that a cell
+// takes grow like a power of its estimate, since a step size far below the
+// others' at the hand-off is mostly that of a transient: tb.auto_pow, below the
+// slopes of the logarithms (0.67 to 0.78 for 9 species over hot and stress
+// fields, 0.45 to 0.60 for 32), as the largest estimates are the least certain.
+// Measured (ms; cooperative against per lane, the kernel it takes marked):
+//   cells x sub-calls       16,000      27,000      40,000      50,000      65,536     100,000
+//   hot                 *1.0   2.7  *1.4   3.1  *2.0   3.2  *2.4   3.0   3.1  *3.1   4.6  *3.2
+//   stress              *0.9   2.7  *1.1   2.8  *1.4   2.8  *1.7   2.8  *2.1   2.8   3.0  *2.9
+//   ignition x 100      *5.7   7.4   8.6  *7.5  11.6  *7.5  13.5  *7.6  17.6  *7.6  25.4  *10.4
+//   ignition x 30       *2.1   3.9   3.3  *4.0   4.5  *4.0   5.2  *4.0   6.6  *4.0   9.7  *5.5
+//   scattered x 100     *5.9  12.1  *9.0  12.2 *12.0  12.3  14.1 *12.3  18.0 *12.6  26.3 *13.3
+//   hot x 10            *7.0  22.3 *10.2  22.2 *13.7  23.2  17.0 *23.2 *21.8  24.6  31.7 *24.6
+//   stress x 10         *7.2  23.2  *9.3  25.5 *11.7  26.5 *14.1  25.9 *17.2  25.9 *24.7  26.5
+//   hot, dt/4 x 4       *1.0   2.7  *1.4   3.2  *2.0   3.3  *2.4   3.0  *3.0   3.1  *4.4   3.0
+// and 32 species: 6,000 stress cells *11.8, 24.3; 10,000 *16.1, 24.1; 14,000
+// 21.9, *23.9; 20,000 30.7, *24.1.
 constexpr float kLaneStep = 4.4f;
 
 // Least steps between refills in the resumption, whose cells have tens of
@@ -216,7 +239,7 @@ constexpr int kResumeChunk = 2;
 
 __device__ __forceinline__ bool coop_pays(const TailBuf& tb) {
   float sum, top;
-  tail_estimate(tb.btot, sum, top);
+  tail_estimate(tb.btot, tb.auto_pow, sum, top);
   return fmaxf(sum / tb.auto_coop, top) <= fmaxf(sum / tb.auto_lane, kLaneStep * top);
 }
 
@@ -226,10 +249,11 @@ __device__ __forceinline__ bool coop_pays(const TailBuf& tb) {
 // range per bucket (one atomic per bucket and block) and writes the record
 // indices into tb.order.  It reads the record count on the device, so a captured
 // launch sequence serves any list length.  tail_scatter also decides which kernel finishes
-// the list: at most tb.cap records go to the cooperative kernel (split =
-// count), more are resumed one per lane (split = 0); several lanes per cell
-// only pay while the list is short next to the chip, and the choice depends
-// only on the list's length, so on the input.  Records with equal keys keep
+// the list: the cooperative kernel (split = count) when it has at most tb.cap
+// records and, with tb.auto_coop, that kernel is expected to end it first
+// (coop_pays), else one cell per lane (split = 0); several lanes per cell only
+// pay while the list is short next to the chip, and the choice depends on the
+// list's length and keys, so on the input alone.  Records with equal keys keep
 // no particular order: a cell's integration does not depend on when or by
 // which lanes it runs.
 constexpr int kSortBlock = 1024;
@@ -563,7 +587,10 @@ __global__ __launch_bounds__(LB) void lsrk_persistent(PoolArgs a) {
       float est = 0.f;
       if (item >= 0) {
         const BoxDesc& bd = box_ref(a, bx);
-        est = (float)((bd.n_sub - sub) * bd.dt - t) * __builtin_amdgcn_rcpf((float)h);
+        const int later = bd.n_sub - 1 - sub;
+        const float inv_h = __builtin_amdgcn_rcpf((float)h);
+        est = (float)(bd.dt - t) * inv_h;  // (tail_steps_left in floats)
+        est += (float)later * fmaxf(1.f, __builtin_amdgcn_sqrtf((float)bd.dt * inv_h));
       }
       if (__any(est >= prio)) __builtin_amdgcn_s_setprio(3);
       else if (__any(est >= 0.5f * prio)) __builtin_amdgcn_s_setprio(2);
@@ -620,7 +647,7 @@ __global__ __launch_bounds__(LB) void lsrk_persistent(PoolArgs a) {
           a.tail.sub[r] = sub;
           a.tail.base[r] = base;
         }
-        const int key = tail_key((bd.n_sub - sub) * bd.dt - t, h);
+        const int key = tail_key(tail_steps_left(bd.dt - t, bd.dt, bd.n_sub - 1 - sub, h));
         a.tail.key[r] = key;
         atomicAdd(&s_hist[key], 1u);
         item = -1;
@@ -1254,17 +1281,16 @@ int tuned_key(int64_t total, const chem_opts* o) {
 //   enough that its order by remaining steps is a good estimate: 65,000-cell
 //   front 1,440 -> 860, 65,536 cells x 100 calls (profile of one ignition)
 //   19,100 -> 9,800.
-//   The list goes to the cooperative kernel when it is at most 192 cells per
-//     CU (32 above 16 species, where a cell takes a whole wave) and that kernel
-//     is expected to end it sooner (coop_pays).
+//   The list goes to the cooperative kernel when that kernel is expected to end
+//     it sooner (coop_pays), whatever its length.
 //   order: grouping by NASA-7 range pays its two passes from about two
 //     million cells on (4.2 M cells 24,800 -> 23,900, 2.5 M 14,880 -> 14,350;
 //     a 1400 x 1000 front 1,700 -> 1,730, 200,000 cells of one step each 106
 //     -> 116).
-struct Launch { bool direct; int block, chunk, tail, cap, order; float auto_coop, auto_lane; };
+struct Launch { bool direct; int block, chunk, tail, cap, order; float auto_coop, auto_lane, auto_pow; };
 
 Launch default_launch(chem_mech m, int64_t total, const chem_opts* o) {
-  Launch l{false, kDefaultBlock, kDefaultChunk, kDefaultTail, kDefaultTailCap, 0, 0.f, 0.f};
+  Launch l{false, kDefaultBlock, kDefaultChunk, kDefaultTail, kDefaultTailCap, 0, 0.f, 0.f, 1.f};
   const bool asked = o && (o->block_size || o->chunk_steps || o->tail_steps || o->tail_cap ||
                            o->pool_order || o->fixed_steps > 0 || o->scheme != SCHEME_LSRK);
   if (asked || m->tuned.count(tuned_key(total, o))) return l;
@@ -1273,9 +1299,10 @@ Launch default_launch(chem_mech m, int64_t total, const chem_opts* o) {
   l.block = wide ? 128 : 256;
   l.chunk = wide ? 2 : 1;
   l.tail = wide ? 8 : 4;
-  l.cap = wide ? 32 : 192;
+  l.cap = -1;
   l.auto_coop = (wide ? 2.3f : 15.f) * m->n_cu;
   l.auto_lane = (wide ? 50.f : 75.f) * m->n_cu;
+  l.auto_pow = wide ? 0.45f : 0.65f;
   if (total >= (wide ? int64_t(1) << 17 : int64_t(1) << 21)) l.order = ORDER_RANGE;
   return l;
 }
@@ -1322,6 +1349,7 @@ void set_finisher(chem_mech m, TailBuf& tb, int64_t total, const chem_opts* o) {
   tb.cap = pick_cap(m, total, o);
   tb.auto_coop = l.auto_coop;
   tb.auto_lane = l.auto_lane;
+  tb.auto_pow = l.auto_pow;
 }
 
 void pick_launch(chem_mech m, int64_t total, const chem_opts* o, int* block, int* chunk) {
@@ -1342,7 +1370,7 @@ int grid_for(chem_mech m, int block, int64_t total, int scheme);
 // The flow step's launches: pool reset + persistent kernel, then, with a
 // hand-off point, the tail sort, the cooperative kernel and the per-lane
 // resumption of the list (exactly one of the last two does work, chosen by
-// the list's length against a.tail.cap).  Timed calls record m->tev: [0]
+// tail_scatter).  Timed calls record m->tev: [0]
 // before the persistent kernel, [1] after it, [2] after the tail sort, [3]
 // after the cooperative kernel, [4] after the resumption.
 hipError_t launch_step(chem_mech m, PoolArgs& a, int block, int grid, hipStream_t s,

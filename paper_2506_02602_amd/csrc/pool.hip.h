@@ -65,8 +65,9 @@ struct TailBuf {
                           // a function of the input only)
   // auto_coop > 0: and only when it is expected to end first (coop_pays): how
   // many steps the chip finishes, cooperatively and one cell per lane, in the
-  // time of one step of a lone cooperative group
-  float auto_coop, auto_lane;
+  // time of one step of a lone cooperative group, and the power of a cell's
+  // estimate that its steps grow like
+  float auto_coop, auto_lane, auto_pow;
 };
 
 struct PoolArgs {

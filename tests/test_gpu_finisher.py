@@ -1,0 +1,58 @@
+"""Which kernel finishes the tail list of a call that names no launch option:
+the estimate of the list's steps decides, whatever the list's length, also
+where the cells have many sub-calls to go."""
+import numpy as np
+import pytest
+
+from paper_2506_02602_amd import workloads as wl
+
+from gpu_common import to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def field(cg, gm, path, make, n):
+    """(state, dt, sub-calls) of n cells."""
+    if make == "calls":
+        return wl.diverge_box(path, 1.0, shape=(16, 256, n // 4096)), wl.DIVERGE_DT, wl.DIVERGE_CALLS
+    if make == "stress":
+        return wl.stress_3d(path, shape=(n, 1, 1), seed=92), wl.DT_FLOW, 1
+    s0, hot = wl.front_2d(path, nx=1024, ny=1024, seed=91)
+    hs = np.ascontiguousarray(s0[:, hot])
+    pick = np.arange(hs.shape[1])
+    if make == "alike":
+        import torch
+        counts = torch.zeros(2 * hs.shape[1], dtype=torch.int32, device="cuda")
+        cg.chem_integrate(gm, to_gpu(hs), wl.DT_FLOW, cg.make_opts(tail_steps=-1), counts=counts)
+        c = counts.cpu().numpy().reshape(2, -1).sum(axis=0)
+        pick = np.flatnonzero((c >= 20) & (c <= 24))
+    return np.ascontiguousarray(hs[:, np.resize(pick, n)]), wl.DT_FLOW, 1
+
+
+@pytest.mark.parametrize("make,n,coop", [
+    ("alike", 60000, False),    # short of the longest cell's share: throughput decides
+    ("hot", 40000, True),       # the longest cells decide
+    ("stress", 65536, True),
+    ("calls", 16384, True),     # 100 sub-calls per cell
+    ("calls", 40960, False)])
+def test_finisher_by_estimate(mech9_path, make, n, coop):
+    """Where one finisher is clearly the faster (by 1.3 and more), the list goes
+    to it, and gives its bits."""
+    import torch
+    from paper_2506_02602_amd import chemgpu as cg
+    gm = cg.chem_mech_load(mech9_path)
+    cg.chem_workspace_reserve(gm, n)
+    s, dt, n_sub = field(cg, gm, mech9_path, make, n)
+    out = []
+    cg.chem_set_kernel_timing(gm, True)
+    for opts in (cg.make_opts(), cg.make_opts(tail_steps=4, tail_cap=-1 if coop else 1)):
+        st = to_gpu(s)
+        cg.chem_integrate_batched(gm, [dict(state=st, dt=dt, n_sub=n_sub)], opts)
+        torch.cuda.synchronize()
+        stats = cg.chem_tail_stats(gm)
+        print(f"[finisher] {make} {n}: {stats}", flush=True)
+        assert stats["handed_over"] > n // 4
+        assert stats["cooperative"] == (stats["handed_over"] if coop else 0)
+        out.append(st)
+    assert torch.equal(out[0], out[1])
+    gm.close()
