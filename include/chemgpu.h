@@ -57,29 +57,29 @@ extern "C" {
 
 typedef struct chem_mech_s *chem_mech; /* opaque, owned by the library */
 
-/* Integration options; a zero field selects the default.  An LSRK call whose
- * launch fields (block_size, chunk_steps, tail_steps, tail_cap, pool_order)
- * are all 0 and for whose size nothing is tuned takes the launch its size
- * calls for: a pool of at most the cooperative kernel's groups on the chip
- * (6,144 cells of 9 species, 2,048 of 32) goes to that kernel as it is; a
- * larger one starts one cell per lane, hands over early, and the device picks
- * the kernel that is expected to finish the handed-over cells first. */
+/* Integration options; a zero field selects the default: the value tuned for
+ * the call's size, else (LSRK scheme without fixed_steps) the one its size
+ * calls for, else block 128, chunk 8, no order.  The size rule: a pool of at
+ * most the cooperative kernel's groups on the chip (6,144 cells of 9 species,
+ * 2,048 of 32) goes to that kernel as it is, unless tail_steps or tail_cap is
+ * set; a larger one starts one cell per lane, hands over after 4 steps (8
+ * above 16 species), and the device picks the kernel that is expected to finish
+ * the handed-over cells first.  Setting one of block_size, chunk_steps (> 0)
+ * and pool_order changes nothing else, and no result. */
 typedef struct {
     double rtol;         /* relative tolerance of Eq. 22 (default 1e-8) */
     double atol;         /* absolute tolerance of Eq. 22, every component (default 1e-10) */
     int32_t max_steps;   /* accepted + rejected steps per cell (default 100000) */
-    int32_t chunk_steps; /* steps a lane takes between compaction points; 0 = tuned default,
+    int32_t chunk_steps; /* steps a lane takes between compaction points; 0 = default,
                             < 0 = no compaction (one cell per lane for the whole step) */
-    int32_t block_size;  /* threads per block, multiple of 64 up to 512 (0 = tuned default) */
+    int32_t block_size;  /* threads per block, multiple of 64 up to 512 (0 = default) */
     int32_t fixed_steps; /* > 0: test mode, exactly this many steps of dt/fixed_steps, no control */
     int32_t tail_steps;  /* a cell still stepping after this many steps (accepted + rejected,
-                            over all sub-calls) is handed over; if at most tail_cap cells
-                            per CU are handed over they are finished by the cooperative
-                            kernel, several lanes per cell, otherwise one cell per lane as
-                            before.  0 = tuned default, < 0 = never.  The hand-off point and
+                            over all sub-calls) is handed over; the cooperative kernel,
+                            several lanes per cell, or the per-lane one finishes it (see
+                            tail_cap).  0 = default, < 0 = never.  The hand-off point and
                             that choice depend only on the input, so results do not depend
-                            on block_size or chunk_steps.  (Without a tuned default or
-                            the size rule above: after 32 steps) */
+                            on block_size or chunk_steps */
     int32_t scheme;      /* 0: the paper's low-storage LSRK4(3)5 two-register scheme (Eq. 21);
                             1: the full-storage Runge-Kutta-Fehlberg 4(5) comparison scheme
                             (six stages, all stage vectors kept; same controller with
@@ -91,9 +91,9 @@ typedef struct {
                             mechanisms of at most 15 species (CHEM_EUNSUPPORTED otherwise)
                             and run with block_size <= 256 (CHEM_EINVAL otherwise) */
     int32_t tail_cap;    /* most handed-over cells per CU that the cooperative kernel takes
-                            (see tail_steps): 0 = the tuned value, else the size rule's,
-                            else 64,
-                            > 0 = that many, < 0 = no limit */
+                            (see tail_steps): > 0 = that many, < 0 = no limit, 0 = the
+                            tuned value, else whatever their number if it is expected to
+                            finish them first */
     int32_t pool_order;  /* 1: before the step, cells expected to take many steps (a step
                             hint below dt/8 over the flow step, or without a usable hint
                             T >= 1000 K) are dealt round-robin over the first work claim of

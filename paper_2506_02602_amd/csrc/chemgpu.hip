@@ -1265,11 +1265,15 @@ int tuned_key(int64_t total, const chem_opts* o) {
   return size_bucket(total) * 4 + (o ? o->scheme : SCHEME_LSRK);
 }
 
-// The launch of a call that leaves every launch field of its options 0 and has
-// no tuned one (LSRK scheme; the constants above otherwise).  Measured on
-// fields of 9 species (us; old: block 128, chunk 8, hand-off after 32 steps,
-// cap 64, one launch sequence for every size; new: as it was first, later
-// kernels are faster on either side):
+// How a call is launched.  direct: its cells go to the cooperative kernel as
+// they are; cap: most handed-over cells that the cooperative kernel takes;
+// auto_*: see TailBuf.
+struct Launch { bool direct; int block, chunk, tail, cap, order; float auto_coop, auto_lane, auto_pow; };
+
+// The launch that a call's size calls for (LSRK scheme).  Measured on fields of
+// 9 species (us; old: block 128, chunk 8, hand-off after 32 steps, cap 64, one
+// launch sequence for every size; new: as it was first, later kernels are
+// faster on either side):
 //   direct: a pool no larger than the cooperative kernel's groups on the chip
 //     (6,144; 2,048 for 32 species) goes to that kernel as it is, one launch,
 //     no per-lane steps: 64 hot cells 1,042 -> 640, 4,096 cells of one step
@@ -1287,82 +1291,56 @@ int tuned_key(int64_t total, const chem_opts* o) {
 //     million cells on (4.2 M cells 24,800 -> 23,900, 2.5 M 14,880 -> 14,350;
 //     a 1400 x 1000 front 1,700 -> 1,730, 200,000 cells of one step each 106
 //     -> 116).
-struct Launch { bool direct; int block, chunk, tail, cap, order; float auto_coop, auto_lane, auto_pow; };
-
-Launch default_launch(chem_mech m, int64_t total, const chem_opts* o) {
-  Launch l{false, kDefaultBlock, kDefaultChunk, kDefaultTail, kDefaultTailCap, 0, 0.f, 0.f, 1.f};
-  const bool asked = o && (o->block_size || o->chunk_steps || o->tail_steps || o->tail_cap ||
-                           o->pool_order || o->fixed_steps > 0 || o->scheme != SCHEME_LSRK);
-  if (asked || m->tuned.count(tuned_key(total, o))) return l;
+Launch size_launch(chem_mech m, int64_t total) {
   const bool wide = m->entry->coop_groups == 1;  // a whole wave per cell
+  Launch l{};
   l.direct = total <= m->coop_slots;
   l.block = wide ? 128 : 256;
   l.chunk = wide ? 2 : 1;
   l.tail = wide ? 8 : 4;
-  l.cap = -1;
+  l.cap = INT32_MAX;
+  l.order = total >= (wide ? int64_t(1) << 17 : int64_t(1) << 21) ? ORDER_RANGE : 0;
   l.auto_coop = (wide ? 2.3f : 15.f) * m->n_cu;
   l.auto_lane = (wide ? 50.f : 75.f) * m->n_cu;
   l.auto_pow = wide ? 0.45f : 0.65f;
-  if (total >= (wide ? int64_t(1) << 17 : int64_t(1) << 21)) l.order = ORDER_RANGE;
   return l;
 }
 
-int pick_tail(chem_mech m, int64_t total, const chem_opts* o) {
-  if (o && o->fixed_steps > 0) return 0;
-  if (o && o->scheme != SCHEME_LSRK) return 0;  // the cooperative kernel runs the LSRK scheme
-  int t = o ? o->tail_steps : 0;
-  if (t == 0) {
-    auto it = m->tuned.find(tuned_key(total, o));
-    t = (it != m->tuned.end() && it->second.tail != 0) ? it->second.tail
-                                                       : default_launch(m, total, o).tail;
-  }
-  return t > 0 ? t : 0;
+// A call's launch: what its size calls for (fixed steps and the other schemes,
+// which have no hand-off: the constants above), the fields that are tuned for
+// its size in place of those, and the fields that its options name in place of
+// either.  A field changes what it stands for and nothing else, so block size,
+// chunk and order, which change no result, leave the hand-off, the finisher and
+// the direct launch as they are; these three follow tail_steps and tail_cap.
+Launch pick_launch(chem_mech m, int64_t total, const chem_opts* o) {
+  const bool handoff = !o || (o->scheme == SCHEME_LSRK && o->fixed_steps == 0);
+  Launch l = handoff ? size_launch(m, total)
+                     : Launch{false, kDefaultBlock, kDefaultChunk, 0, 0, 0, 0.f, 0.f, 1.f};
+  auto take = [&](int block, int chunk, int tail, int cap, int order) {
+    if (block) l.block = block;
+    if (chunk) l.chunk = chunk;
+    if (order) l.order = order > 0 ? order : 0;
+    if (!handoff) return;
+    if (tail) l.tail = std::max(tail, 0);
+    if (cap) {
+      l.cap = cap < 0 ? INT32_MAX : (int)std::min<int64_t>((int64_t)cap * m->n_cu, INT32_MAX);
+      l.auto_coop = 0.f;  // the count alone decides
+    }
+    if (tail || cap) l.direct = false;
+  };
+  auto it = m->tuned.find(tuned_key(total, o));
+  if (it != m->tuned.end())
+    take(it->second.block, it->second.chunk, it->second.tail, it->second.cap, it->second.order);
+  if (o) take(o->block_size, o->chunk_steps, o->tail_steps, o->tail_cap, o->pool_order);
+  return l;
 }
 
-// Pool order: ORDER_DEAL, ORDER_RANGE or ORDER_RANGE_DEFER (chem_opts.pool_order
-// 1, 2 or 3), off (< 0), else the tuned choice, else the default.  Returns 0
-// for off.
-int pick_order(chem_mech m, int64_t total, const chem_opts* o) {
-  int v = o ? o->pool_order : 0;
-  if (v == 0) {
-    auto it = m->tuned.find(tuned_key(total, o));
-    v = it != m->tuned.end() ? it->second.order : default_launch(m, total, o).order;
-  }
-  return v == ORDER_DEAL || v == ORDER_RANGE || v == ORDER_RANGE_DEFER ? v : 0;
-}
-
-// Most handed-over cells the cooperative kernel takes, over the whole chip.
-int pick_cap(chem_mech m, int64_t total, const chem_opts* o) {
-  int c = o ? o->tail_cap : 0;
-  if (c == 0) {
-    auto it = m->tuned.find(tuned_key(total, o));
-    c = (it != m->tuned.end() && it->second.cap != 0) ? it->second.cap
-                                                      : default_launch(m, total, o).cap;
-  }
-  if (c < 0) return INT32_MAX;
-  return (int)std::min<int64_t>((int64_t)c * m->n_cu, INT32_MAX);
-}
-
-// Which kernel finishes the tail list.
-void set_finisher(chem_mech m, TailBuf& tb, int64_t total, const chem_opts* o) {
-  const Launch l = default_launch(m, total, o);
-  tb.cap = pick_cap(m, total, o);
+// The tail list's finisher as the launch has it.
+void set_finisher(TailBuf& tb, const Launch& l) {
+  tb.cap = l.cap;
   tb.auto_coop = l.auto_coop;
   tb.auto_lane = l.auto_lane;
   tb.auto_pow = l.auto_pow;
-}
-
-void pick_launch(chem_mech m, int64_t total, const chem_opts* o, int* block, int* chunk) {
-  *block = (o && o->block_size) ? o->block_size : 0;
-  *chunk = (o && o->chunk_steps) ? o->chunk_steps : 0;
-  auto it = m->tuned.find(tuned_key(total, o));
-  if (it != m->tuned.end()) {
-    if (!*block) *block = it->second.block;
-    if (!*chunk) *chunk = it->second.chunk;
-  }
-  const Launch l = default_launch(m, total, o);
-  if (!*block) *block = l.block;
-  if (!*chunk) *chunk = l.chunk;
 }
 
 int grid_for(chem_mech m, int block, int64_t total, int scheme);
@@ -1434,8 +1412,7 @@ hipError_t launch_step(chem_mech m, PoolArgs& a, int block, int grid, hipStream_
   return hipSuccess;
 }
 
-// The cooperative kernel over the pool's cells (default_launch's direct
-// case): as few waves as hold them, a group per cell, spread over the CUs
+// The cooperative kernel over the pool's cells (a direct launch): as few waves as hold them, a group per cell, spread over the CUs
 // before the groups of a wave are filled.  Timed calls record it as the
 // cooperative launch.
 hipError_t launch_direct_coop(chem_mech m, PoolArgs& a, hipStream_t s, bool timed = false) {
@@ -1455,15 +1432,14 @@ hipError_t launch_direct_coop(chem_mech m, PoolArgs& a, hipStream_t s, bool time
 // (calls that may run concurrently on one mechanism each bring their own).
 int run_pool_with(chem_mech m, PoolArgs& a, const chem_opts* o, hipStream_t s,
                   unsigned long long* next, TailStore& tail, OrderStore* order, bool timed) {
-  int block, chunk;
-  pick_launch(m, a.total, o, &block, &chunk);
-  if (m->entry->lds_per_lane() * block > 65536)
+  const Launch l = pick_launch(m, a.total, o);
+  if (m->entry->lds_per_lane() * l.block > 65536)
     return fail(CHEM_EINVAL, "block_size too large for this mechanism's LDS compaction slots");
   if (a.total > 0x7fffffff) return fail(CHEM_EINVAL, "more than 2^31-1 work items in one call");
-  int rc0 = check_scheme_launch(m, o, block);
+  int rc0 = check_scheme_launch(m, o, l.block);
   if (rc0) return rc0;
   timed = timed && m->timing;
-  if (a.total > 0 && default_launch(m, a.total, o).direct) {
+  if (a.total > 0 && l.direct) {
     hipError_t e = launch_direct_coop(m, a, s, timed);
     if (e != hipSuccess) return hip_fail(e, "launch cooperative kernel");
     if (timed) {
@@ -1473,16 +1449,16 @@ int run_pool_with(chem_mech m, PoolArgs& a, const chem_opts* o, hipStream_t s,
     return CHEM_OK;
   }
   a.next = next;
-  a.chunk = chunk > 0 ? chunk : kDefaultChunk;
-  a.tail_steps = pick_tail(m, a.total, o);
+  a.chunk = l.chunk > 0 ? l.chunk : kDefaultChunk;
+  a.tail_steps = l.tail;
   if (a.tail_steps > 0) {
     if (!tail.mem || a.total > tail.cap)
       return fail(CHEM_ECAPACITY, "more cells than the reserved tail records");
     a.tail = tail.view();
-    set_finisher(m, a.tail, a.total, o);
+    set_finisher(a.tail, l);
   }
   OrderBuf ob{};
-  const int omode = order ? pick_order(m, a.total, o) : 0;
+  const int omode = order ? l.order : 0;
   const bool ordered = omode != 0;
   if (ordered) {
     if (!order->mem || a.total > order->cap)
@@ -1492,7 +1468,7 @@ int run_pool_with(chem_mech m, PoolArgs& a, const chem_opts* o, hipStream_t s,
     ob.defer = omode == ORDER_RANGE_DEFER;
     ob.t_split = m->entry->t_split;
   }
-  hipError_t e = launch_step(m, a, block, grid_for(m, block, a.total, a.scheme), s,
+  hipError_t e = launch_step(m, a, l.block, grid_for(m, l.block, a.total, a.scheme), s,
                              ordered ? &ob : nullptr, timed);
   if (e != hipSuccess) return hip_fail(e, "launch integrator kernels");
   if (timed) {
@@ -2053,12 +2029,11 @@ int chem_integrate(chem_mech m, double* state, int64_t ld, int64_t n_cells, doub
   a.c = make_control(opts);
   a.fixed_steps = opts ? opts->fixed_steps : 0;
   a.scheme = opts ? opts->scheme : SCHEME_LSRK;
-  int block, chunk;
-  pick_launch(m, n_cells, opts, &block, &chunk);
-  if (chunk < 0) {
-    rc = check_scheme_launch(m, opts, block);
+  const Launch l = pick_launch(m, n_cells, opts);
+  if (l.chunk < 0) {
+    rc = check_scheme_launch(m, opts, l.block);
     if (rc) return rc;
-    hipError_t e = m->entry->launch_direct(a, block, s);
+    hipError_t e = m->entry->launch_direct(a, l.block, s);
     if (e != hipSuccess) return hip_fail(e, "launch lsrk_direct");
     return CHEM_OK;
   }
@@ -2088,12 +2063,11 @@ int chem_integrate_noalloc(chem_mech m, double* state, int64_t ld, int64_t n_cel
   a.c = make_control(opts);
   a.fixed_steps = opts ? opts->fixed_steps : 0;
   a.scheme = opts ? opts->scheme : SCHEME_LSRK;
-  int block, chunk;
-  pick_launch(m, n_cells, opts, &block, &chunk);
-  if (chunk < 0) {
-    rc = check_scheme_launch(m, opts, block);
+  const Launch l = pick_launch(m, n_cells, opts);
+  if (l.chunk < 0) {
+    rc = check_scheme_launch(m, opts, l.block);
     if (rc) return rc;
-    hipError_t e = m->entry->launch_direct(a, block, s);
+    hipError_t e = m->entry->launch_direct(a, l.block, s);
     if (e != hipSuccess) return hip_fail(e, "launch lsrk_direct");
     return CHEM_OK;
   }
@@ -2188,11 +2162,10 @@ int chem_graph_capture_batched(chem_mech m, const chem_box* boxes, int32_t n_box
   if (rc) return rc;
   if (total == 0) return fail(CHEM_EINVAL, "chem_graph_capture_batched: no cells");
   if (total > 0x7fffffff) return fail(CHEM_EINVAL, "more than 2^31-1 work items in one call");
-  int block, chunk;
-  pick_launch(m, total, opts, &block, &chunk);
-  if (m->entry->lds_per_lane() * block > 65536)
+  const Launch l = pick_launch(m, total, opts);
+  if (m->entry->lds_per_lane() * l.block > 65536)
     return fail(CHEM_EINVAL, "block_size too large for this mechanism's LDS compaction slots");
-  rc = check_scheme_launch(m, opts, block);
+  rc = check_scheme_launch(m, opts, l.block);
   if (rc) return rc;
   chem_graph g = new (std::nothrow) chem_graph_s();
   if (!g) return fail(CHEM_ENOMEM, "chem_graph_capture_batched: host allocation");
@@ -2204,13 +2177,12 @@ int chem_graph_capture_batched(chem_mech m, const chem_box* boxes, int32_t n_box
   if (e != hipSuccess) return bail(e, "hipMalloc(graph box table)");
   e = hipMalloc(&g->d_next, sizeof(unsigned long long));
   if (e != hipSuccess) return bail(e, "hipMalloc(graph pool counter)");
-  const bool direct = default_launch(m, total, opts).direct;
-  const int tail_steps = direct ? 0 : pick_tail(m, total, opts);
+  const int tail_steps = l.direct ? 0 : l.tail;
   if (tail_steps > 0) {
     rc = alloc_tail(g->tail, total, m->entry->tail_rd);
     if (rc) { chem_graph_destroy(g); return rc; }
   }
-  const int omode = pick_order(m, total, opts);
+  const int omode = l.direct ? 0 : l.order;
   const bool ordered = omode != 0;
   if (ordered) {
     rc = alloc_order(g->order, total);
@@ -2229,15 +2201,15 @@ int chem_graph_capture_batched(chem_mech m, const chem_box* boxes, int32_t n_box
   a.total = total;
   a.next = g->d_next;
   a.c = make_control(opts);
-  a.chunk = chunk > 0 ? chunk : kDefaultChunk;
+  a.chunk = l.chunk > 0 ? l.chunk : kDefaultChunk;
   a.fixed_steps = opts ? opts->fixed_steps : 0;
   a.scheme = opts ? opts->scheme : SCHEME_LSRK;
   a.tail_steps = tail_steps;
   if (tail_steps > 0) {
     a.tail = g->tail.view();
-    set_finisher(m, a.tail, total, opts);
+    set_finisher(a.tail, l);
   }
-  const int grid = grid_for(m, block, total, a.scheme);
+  const int grid = grid_for(m, l.block, total, a.scheme);
   hipStream_t cs;
   e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
   if (e != hipSuccess) return bail(e, "hipStreamCreate(capture)");
@@ -2247,8 +2219,8 @@ int chem_graph_capture_batched(chem_mech m, const chem_box* boxes, int32_t n_box
   ob.mode = omode == ORDER_RANGE_DEFER ? ORDER_RANGE : omode;
   ob.defer = omode == ORDER_RANGE_DEFER;
   ob.t_split = m->entry->t_split;
-  hipError_t le = direct ? launch_direct_coop(m, a, cs)
-                         : launch_step(m, a, block, grid, cs, ordered ? &ob : nullptr);
+  hipError_t le = l.direct ? launch_direct_coop(m, a, cs)
+                           : launch_step(m, a, l.block, grid, cs, ordered ? &ob : nullptr);
   e = hipStreamEndCapture(cs, &g->graph);
   (void)hipStreamDestroy(cs);
   if (le != hipSuccess) return bail(le, "launch integrator kernels (capture)");

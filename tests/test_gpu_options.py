@@ -1,0 +1,52 @@
+"""Launch fields of chem_opts: each changes what it stands for and nothing else,
+so the ones that only schedule leave every bit of a default call as it is."""
+import numpy as np
+import pytest
+
+from paper_2506_02602_amd import workloads as wl
+
+from gpu_common import to_gpu
+
+pytestmark = pytest.mark.gpu
+
+FIELDS = [dict(block_size=64), dict(block_size=128), dict(block_size=512), dict(chunk_steps=1),
+          dict(chunk_steps=8), dict(pool_order=-1), dict(pool_order=1), dict(pool_order=3),
+          dict(block_size=192, chunk_steps=4, pool_order=2)]
+
+
+@pytest.mark.parametrize("n", [2000, 30000])
+@pytest.mark.parametrize("entry", ["integrate", "noalloc", "batched", "graph"])
+def test_scheduling_fields_keep_the_bits(mech9_path, n, entry):
+    """A small pool (the cooperative kernel alone) and one with a tail list."""
+    import torch
+    from paper_2506_02602_amd import chemgpu as cg
+    s0, hot = wl.front_2d(mech9_path, nx=1024, ny=1024, seed=93)
+    k = n // 2
+    s = np.ascontiguousarray(np.concatenate([s0[:, hot][:, :k], s0[:, ~hot][:, :n - k]], axis=1))
+    gm = cg.chem_mech_load(mech9_path)
+    cg.chem_workspace_reserve(gm, n)
+
+    def run(**kw):
+        o = cg.make_opts(**kw)
+        st = to_gpu(s)
+        counts = torch.zeros(2 * n, dtype=torch.int32, device="cuda")
+        box = [dict(state=st, dt=wl.DT_FLOW, n_sub=1, counts=counts)]
+        if entry == "integrate":
+            cg.chem_integrate(gm, st, wl.DT_FLOW, o, counts=counts)
+        elif entry == "noalloc":
+            cg.chem_integrate_noalloc(gm, st, wl.DT_FLOW, o, counts=counts)
+        elif entry == "batched":
+            cg.chem_integrate_batched(gm, box, o)
+        else:
+            g = cg.chem_graph_capture_batched(gm, box, o)
+            g.launch()
+            torch.cuda.synchronize()
+            g.close()
+        torch.cuda.synchronize()
+        return st, counts
+    ref = run()
+    assert int(ref[1].max()) > 40      # past every hand-off point
+    for kw in FIELDS:
+        got = run(**kw)
+        assert torch.equal(ref[0], got[0]) and torch.equal(ref[1], got[1]), kw
+    gm.close()
