@@ -33,6 +33,7 @@
 #include <vector>
 
 #include "chemgpu.h"
+#include "launch.h"
 #include "advance.hip.h"
 #include "pool.hip.h"
 
@@ -119,7 +120,8 @@ struct Slots {
   static constexpr int N1 = M::NS + 1;
   static constexpr int ND = N1 + 3;
   static constexpr int NI = 6;  // item, nacc, nrej, sub, base, box
-  static size_t bytes(int block) { return (size_t)block * (ND * sizeof(double) + NI * sizeof(int)); }
+  static constexpr size_t bytes(int block) { return slot_bytes(M::NS, block); }
+  static_assert(bytes(64) == 64 * (ND * sizeof(double) + NI * sizeof(int)), "slot_bytes");
 };
 
 __global__ void eval_math_kernel(int fn, const double* x, double* y, int64_t n) {
@@ -845,7 +847,6 @@ struct MechEntry {
   hipError_t (*launch_prim_to_cons)(const double*, const int8_t*, int64_t, double*, int64_t,
                                     int32_t*, hipStream_t);
   int (*max_blocks_per_cu)(int block, int scheme);
-  size_t (*lds_per_lane)();
   hipError_t (*launch_surr_infer)(const surr::InferArgs&, int grid, hipStream_t);
   hipError_t (*launch_make_pairs)(const double*, const double*, long, long, double, const double*,
                                   float*, float*, hipStream_t);
@@ -986,16 +987,11 @@ int max_blocks_per_cu(int block, int scheme) {
                                 : max_blocks_per_cu_s<M, SCHEME_LSRK>(block);
 }
 
-template <class M>
-size_t lds_per_lane() {
-  return Slots<M>::bytes(1);
-}
-
 #define CHEM_ENTRY(M) {M::HASH, M::NS, M::NR, M::NAME, M::HAS_JAC, M::T_SPLIT, \
                        &launch_direct<M>, &launch_persistent<M>, \
                        &launch_coop<M>, 64 / M::Coop::G, &coop_groups_per_block<M>, \
                        &launch_cons_to_prim<M>, &launch_prim_to_cons<M>, \
-                       &max_blocks_per_cu<M>, &lds_per_lane<M>, \
+                       &max_blocks_per_cu<M>, \
                        &launch_surr_infer<M>, &launch_make_pairs<M>, &launch_train<M>, \
                        TrainSizes<M>::wtpack_elems, TrainSizes<M>::w4t_ld, TrainSizes<M>::wt4, \
                        TrainSizes<M>::wt2, TailRec<M>::RD},
@@ -1295,7 +1291,7 @@ Launch size_launch(chem_mech m, int64_t total) {
   const bool wide = m->entry->coop_groups == 1;  // a whole wave per cell
   Launch l{};
   l.direct = total <= m->coop_slots;
-  l.block = wide ? 128 : 256;
+  l.block = size_block(m->entry->ns, wide);
   l.chunk = wide ? 2 : 1;
   l.tail = wide ? 8 : 4;
   l.cap = INT32_MAX;
@@ -1314,8 +1310,9 @@ Launch size_launch(chem_mech m, int64_t total) {
 // the direct launch as they are; these three follow tail_steps and tail_cap.
 Launch pick_launch(chem_mech m, int64_t total, const chem_opts* o) {
   const bool handoff = !o || (o->scheme == SCHEME_LSRK && o->fixed_steps == 0);
+  const int block = fit_block(m->entry->ns, kDefaultBlock);
   Launch l = handoff ? size_launch(m, total)
-                     : Launch{false, kDefaultBlock, kDefaultChunk, 0, 0, 0, 0.f, 0.f, 1.f};
+                     : Launch{false, block, kDefaultChunk, 0, 0, 0, 0.f, 0.f, 1.f};
   auto take = [&](int block, int chunk, int tail, int cap, int order) {
     if (block) l.block = block;
     if (chunk) l.chunk = chunk;
@@ -1433,7 +1430,7 @@ hipError_t launch_direct_coop(chem_mech m, PoolArgs& a, hipStream_t s, bool time
 int run_pool_with(chem_mech m, PoolArgs& a, const chem_opts* o, hipStream_t s,
                   unsigned long long* next, TailStore& tail, OrderStore* order, bool timed) {
   const Launch l = pick_launch(m, a.total, o);
-  if (m->entry->lds_per_lane() * l.block > 65536)
+  if (!block_fits(m->entry->ns, l.block))
     return fail(CHEM_EINVAL, "block_size too large for this mechanism's LDS compaction slots");
   if (a.total > 0x7fffffff) return fail(CHEM_EINVAL, "more than 2^31-1 work items in one call");
   int rc0 = check_scheme_launch(m, o, l.block);
@@ -1624,7 +1621,7 @@ int tune_search(chem_mech m, const chem_opts& o, int reps, const TimeOne& time_o
   const bool tune_tail = o.tail_steps == 0 && o.fixed_steps == 0 && o.scheme == SCHEME_LSRK;
   const bool tune_cap = tune_tail && o.tail_cap == 0;
   auto consider = [&](int b, int c, int tl, int cap, int ord) -> int {
-    if (m->entry->lds_per_lane() * b > 65536) return CHEM_OK;
+    if (!block_fits(m->entry->ns, b)) return CHEM_OK;
     if (o.scheme == SCHEME_ROS4 && b > 256) return CHEM_OK;
     chem_opts t = o;
     t.block_size = b;
@@ -1767,7 +1764,7 @@ int tune_search(chem_mech m, const chem_opts& o, int reps, const TimeOne& time_o
       const Seen cur{best_block, best_chunk, best_tail, best_cap, best_order, best_ms};
       std::vector<Seen> cand{cur};
       auto add = [&](int b, int c, int tl, int cap, int ord) {
-        if (m->entry->lds_per_lane() * b > 65536) return;
+        if (!block_fits(m->entry->ns, b)) return;
         if (o.scheme == SCHEME_ROS4 && b > 256) return;
         for (const Seen& w : cand)
           if (w.b == b && w.c == c && w.tl == tl && w.cap == cap && w.ord == ord) return;
@@ -2163,7 +2160,7 @@ int chem_graph_capture_batched(chem_mech m, const chem_box* boxes, int32_t n_box
   if (total == 0) return fail(CHEM_EINVAL, "chem_graph_capture_batched: no cells");
   if (total > 0x7fffffff) return fail(CHEM_EINVAL, "more than 2^31-1 work items in one call");
   const Launch l = pick_launch(m, total, opts);
-  if (m->entry->lds_per_lane() * l.block > 65536)
+  if (!block_fits(m->entry->ns, l.block))
     return fail(CHEM_EINVAL, "block_size too large for this mechanism's LDS compaction slots");
   rc = check_scheme_launch(m, opts, l.block);
   if (rc) return rc;
