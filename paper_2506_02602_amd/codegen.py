@@ -26,11 +26,10 @@ parameter and NASA-7 coefficient is a literal:
   1 ulp);
 * progress q_j = [M]_j (k_f prod c^nu' - k_r prod c^nu''), integer powers as
   products; production rates accumulated straight into N registers;
-* mechanisms of at most ``BASE2_MAX_N`` species form the exponents in base 2
-  and, where the range check of ``_activity_form`` allows, the rates of
+* mechanisms of at most ``CONC_MAX_N`` species take concentrations and, where
+  the range check of ``_activity_form`` allows, form the reverse rates of
   progress from activities c_k exp(g_k/RT), with the exponential the caller
-  passes (a table in LDS or a polynomial, exponents in units of
-  1/``EXP_SCALE``);
+  passes (a table in LDS or a polynomial);
 * dY_k/dt = W_k wdot_k / rho and the constant-volume adiabatic dT/dt.
 
 This parser is the GPU side's own; it shares nothing with the CPU oracle.
@@ -140,24 +139,14 @@ def _powsum(coefs):
     return " + ".join(terms + [lit(coefs[0])])
 
 
-# The exponents of the rates are formed in base 2: an exponential then needs
-# no multiplication by 1/ln 2 and no two-part subtraction of n ln 2 (see
-# exp2_rate), and every constant takes the factor log2(e) here, rounded once.
-# Mechanisms of more than BASE2_MAX_N species keep base e in the per-lane
-# right-hand side: it gained 2 % there, and on 32 species a last-bit change
-# sends one cell in a few hundred thousand through another, equally valid
-# sequence of steps that ends several tolerances away, so their results are
-# kept to the bit.
-BASE2_MAX_N = 16
-# Scale of the activity form's exponents: the entries to an octave of the table
-# of ExpTable (a power of two, so exact).
+# Mechanisms of at most this many species get a right-hand side over
+# concentrations (rhs_c).  The wider ones' results are kept to the bit: on 32
+# species a last-bit change sends one cell in a few hundred thousand through
+# another, equally valid sequence of steps that ends several tolerances away.
+CONC_MAX_N = 16
+# Entries to an octave of the table of ExpTable.
 EXP_SCALE = 4096
 LOG2E = 1 / Fraction("0.693147180559945309417232121458176568075500134360255254120680009")
-
-
-def _b2(x: float, scale: int = 1) -> float:
-    """x log2(e), correctly rounded."""
-    return float(Fraction(x) * LOG2E * scale)
 
 
 def gen_exp2_table() -> str:
@@ -173,28 +162,25 @@ def gen_exp2_table() -> str:
             "".join("    " + ", ".join(out[i:i + 4]) + ",\n" for i in range(0, EXP_SCALE, 4)) + "};\n")
 
 
-def _thermo_block(species, idx, rng, scale, suffix="", den="den"):
+def _thermo_block(species, idx, rng, suffix="", den="den"):
     out = []
-    b2 = (lambda x: _b2(x, scale)) if len(species) <= BASE2_MAX_N else float
     for k in idx:
         a = species[k][rng]
         # h/RT = a1 + a2 T/2 + a3 T^2/3 + a4 T^3/4 + a5 T^4/5 + a6/T
         # (less 1 for the small mechanisms: only h/RT - 1 is used)
-        one = 1.0 if len(species) <= BASE2_MAX_N else 0.0
+        one = 1.0 if len(species) <= CONC_MAX_N else 0.0
         h = _powsum([a[0] - one, a[1] / 2, a[2] / 3, a[3] / 4, a[4] / 5])
-        # g/RT = h/RT - s/R = a1 (1 - ln T) - (a2 T/2 + a3 T^2/6 + a4 T^3/12 + a5 T^4/20) + a6/T - a7,
-        # times log2(e) (small mechanisms)
-        b = [b2(x) for x in a]
-        gp = _powsum([b2(a[1] / 2), b2(a[2] / 6), b2(a[3] / 12), b2(a[4] / 20)])
+        # g/RT = h/RT - s/R = a1 (1 - ln T) - (a2 T/2 + a3 T^2/6 + a4 T^3/12 + a5 T^4/20) + a6/T - a7
+        gp = _powsum([a[1] / 2, a[2] / 6, a[3] / 12, a[4] / 20])
         # c_k (cp_k/R - 1), cp/R = a1 + a2 T + a3 T^2 + a4 T^3 + a5 T^4
         out.append(f"    {den} += c{k} * ({_powsum([a[0] - 1.0] + list(a[1:5]))});")
         decl = "const double " if suffix else ""
         out.append(f"    {decl}h{k}{suffix} = {h} + {lit(a[5])} * invT;")
-        out.append(f"    {decl}g{k}{suffix} = {lit(b[0])} * omlnT - T * ({gp}) + {lit(b[5])} * invT - {lit(b[6])};")
+        out.append(f"    {decl}g{k}{suffix} = {lit(a[0])} * omlnT - T * ({gp}) + {lit(a[5])} * invT - {lit(a[6])};")
     return out
 
 
-def _thermo(species, scale=1):
+def _thermo(species):
     """Range selection made wave-uniform: waves whose lanes all sit in one
     NASA-7 range evaluate that range with literal coefficients; a wave that
     straddles T_mid evaluates both ranges and selects per lane."""
@@ -205,15 +191,15 @@ def _thermo(species, scale=1):
     for gi, (tm, idx) in enumerate(groups.items()):
         L.append(f"    const bool lo{gi} = T < {lit(tm)};")
         L.append(f"    if (__all(lo{gi})) {{")
-        L += ["  " + x for x in _thermo_block(species, idx, "lo", scale)]
+        L += ["  " + x for x in _thermo_block(species, idx, "lo")]
         L.append(f"    }} else if (!__any(lo{gi})) {{")
-        L += ["  " + x for x in _thermo_block(species, idx, "hi", scale)]
+        L += ["  " + x for x in _thermo_block(species, idx, "hi")]
         L.append("    } else {")
         L.append("      double dlo = 0.0, dhi = 0.0;")
         for k in idx:
             L.append("      {")
-            L += ["    " + x for x in _thermo_block(species, [k], "lo", scale, "_l", "dlo")]
-            L += ["    " + x for x in _thermo_block(species, [k], "hi", scale, "_h", "dhi")]
+            L += ["    " + x for x in _thermo_block(species, [k], "lo", "_l", "dlo")]
+            L += ["    " + x for x in _thermo_block(species, [k], "hi", "_h", "dhi")]
             L.append(f"        h{k} = lo{gi} ? h{k}_l : h{k}_h;")
             L.append(f"        g{k} = lo{gi} ? g{k}_l : g{k}_h;")
             L.append("      }")
@@ -318,14 +304,13 @@ def _prod_expr(coef: str, side: dict) -> str:
     return " * ".join(terms)
 
 
-def _lkf_expr(rx: dict, base2: bool) -> str:
-    """log2 k_f = log2 A + b log2 T - (Ea/R) log2(e) / T, or ln k_f."""
-    e = [lit(math.log2(rx["A"]) if base2 else math.log(rx["A"]))]
+def _lkf_expr(rx: dict) -> str:
+    """ln k_f = ln A + b ln T - (Ea/R) / T."""
+    e = [lit(math.log(rx["A"]))]
     if rx["b"] != 0.0:
-        e.append(f"{lit(rx['b'])} * {'lgT' if base2 else 'lnT'}")
+        e.append(f"{lit(rx['b'])} * lnT")
     if rx["Ea"] != 0.0:
-        ea = rx["Ea"] / R_J
-        e.append(f"- {lit(_b2(ea) if base2 else ea)} * invT")
+        e.append(f"- {lit(rx['Ea'] / R_J)} * invT")
     return " + ".join(e).replace("+ -", "-")
 
 
@@ -334,12 +319,10 @@ def _rate_lines(m: dict, orders: list) -> list:
     from its factor order (see _reverse_factors), or through its own
     exponential when orders[j] is None."""
     L = []
-    base2 = len(m["species"]) <= BASE2_MAX_N
-    ex = "exp2_rate" if base2 else "exp_ranged"
     for j, rx in enumerate(m["reactions"]):
         L.append(f"    {{  // reaction {j}")
-        L.append(f"      const double lkf = {_lkf_expr(rx, base2)};")
-        L.append(f"      const double kf = {ex}(lkf);")
+        L.append(f"      const double lkf = {_lkf_expr(rx)};")
+        L.append(f"      const double kf = exp_ranged(lkf);")
         nu = _nu(rx)
         dnu = sum(nu.values())
         if isinstance(orders[j], tuple):
@@ -358,7 +341,7 @@ def _rate_lines(m: dict, orders: list) -> list:
                 sign = "-" if dnu > 0 else "+"
                 mag = abs(dnu)
                 gterms.append(f" {sign} {'' if mag == 1 else lit(float(mag)) + ' * '}lnPRT")
-            L.append(f"      const double kr = {ex}(lkf{''.join(gterms)});")
+            L.append(f"      const double kr = exp_ranged(lkf{''.join(gterms)});")
         q = f"{_prod_expr('kf', rx['reac'])} - {_prod_expr('kr', rx['prod'])}"
         if rx["tb"]:
             mt = " + ".join(f"{lit(a)} * c{k}" for k, a in enumerate(rx["eff"]))
@@ -376,42 +359,34 @@ def _rate_lines(m: dict, orders: list) -> list:
     return L
 
 
-def _t_lines(m: dict, scale: int = 1) -> list:
-    """What the rates and the thermo need of T beside ln T: log2 T, 1/T, 1 - ln
-    T, powers.  Outside (T_RATE_MIN, T_RATE_MAX) the device's ln T is NaN
+def _t_lines(m: dict) -> list:
+    """What the rates and the thermo need of T beside ln T: 1/T, 1 - ln T,
+    powers.  Outside (T_RATE_MIN, T_RATE_MAX) the device's ln T is NaN
     (log_checked): there (far outside the fits) an exponent could leave the
-    range ExpTable and exp2_tab take (exponents below 2^19 and 2^25), and a
-    NaN right-hand side is a rejected step (the factors of the reverse rates
-    leave the double range far above T_RATE_MIN)."""
+    range ExpTable and exp_coop take (2^19 and 2^25 octaves), and a NaN
+    right-hand side is a rejected step (the factors of the reverse rates leave
+    the double range far above T_RATE_MIN)."""
     for T in (T_RATE_MIN, T_RATE_MAX):
-        g = [abs(_b2(_g_rt(sp, T))) for sp in m["species"]]
+        g = [abs(_g_rt(sp, T)) for sp in m["species"]]
         # k_f's with the species' terms of either side (or one species' alone)
-        big = g + [abs(math.log2(rx["A"])) + abs(rx["b"] * math.log2(T)) +
-                   _b2(abs(rx["Ea"]) / R_J) / T +
+        big = g + [abs(math.log(rx["A"])) + abs(rx["b"] * math.log(T)) + abs(rx["Ea"]) / R_J / T +
                    sum(v * g[k] for side in ("reac", "prod") for k, v in rx[side].items())
                    for rx in m["reactions"]]
-        if max(big) > (2.0 ** 31 / EXP_SCALE if len(m["species"]) <= BASE2_MAX_N else 2.0 ** 25):
-            raise ValueError(f"{m['name']}: rate exponents at {T} K leave the range of 2^y")
-    if len(m["species"]) > BASE2_MAX_N:
-        return ["    const double invT = rcp_nr(T);",
-                "    const double omlnT = 1.0 - lnT;",
-                "    const double T2 = T * T, T3 = T2 * T, T4 = T2 * T2;",
-                f"    const double lnPRT = {lit(math.log(m['pstd'] / R_CGS))} - lnT;"]
+        octaves = 2.0 ** 31 / EXP_SCALE if len(m["species"]) <= CONC_MAX_N else 2.0 ** 25
+        if max(big) > octaves * math.log(2.0):
+            raise ValueError(f"{m['name']}: rate exponents at {T} K leave the range of the exponential")
     return ["    const double invT = rcp_nr(T);",
-            f"    const double lgT = lnT * {lit(_b2(1.0, scale))};",
             "    const double omlnT = 1.0 - lnT;",
             "    const double T2 = T * T, T3 = T2 * T, T4 = T2 * T2;",
-            f"    const double lnPRT = {lit(scale * math.log2(m['pstd'] / R_CGS))} - lgT;"]
+            f"    const double lnPRT = {lit(math.log(m['pstd'] / R_CGS))} - lnT;"]
 
 
 def _activity_form(m: dict, rx: dict):
-    """(inverses, factor) of a reaction in the form
+    """(reactants, products, (factor, power)) of a reaction in the form
 
-        q = k_f prod_reac Ei_k (prod_reac a_k - prod_prod a_k factor),
+        q = k_f (prod_reac c_k - prod_reac Ei_k prod_prod a_k factor^power),
 
-    a_k = c_k E_k, E_k = exp(g_k/RT), Ei_k = 1/E_k, factor = (RT/P)^dnu ("" for
-    dnu = 0), the a_k serving both directions of every reaction (with k_f prod
-    Ei_k from one exponential, see _activity_lines).
+    a_k = c_k E_k, E_k = exp(g_k/RT), Ei_k = 1/E_k, factor^power = (RT/P)^dnu.
     None unless every partial product stays within e^+-LN_PARTIAL_MAX on the
     check grid for concentrations between 1e-40 and 1 mol/cm3 (a smaller one
     may underflow to 0, its rate then being below 1e-40 of any other)."""
@@ -432,49 +407,74 @@ def _activity_form(m: dict, rx: dict):
             if max(abs(x) for x in run) > LN_PARTIAL_MAX:
                 return False
         return True
-    if not ok([lkf] + [[-x for x in g[k]] for k in reac]) or \
-            not ok([[-x for x in g[k]] for k in reac] + [lkf]):
-        return None
     p_fac = [[(1 if dnu > 0 else -1) * (math.log(T) - lnP) for T in ts]] * abs(dnu)
+    if not ok([lkf]):
+        return None
     for lc in (0.0, ln_c):
-        if not ok([[x + lc for x in g[k]] for k in reac]) or \
-                not ok([[x + lc for x in g[k]] for k in prod] + p_fac):
+        if not ok([[-x for x in g[k]] for k in reac] + [[x + lc for x in g[k]] for k in prod] + p_fac) or \
+                not ok([[lc] * len(ts)] * len(reac)):
             return None
     return reac, prod, ("RTP" if dnu > 0 else "PRT", abs(dnu))
 
 
-def _activity_lines(m: dict, forms: list) -> list:
+def _lkf_order(rx: dict) -> str:
+    """Order in which the terms of ln k_f, (E) -Ea/RT, (b) b ln T and (A) ln A,
+    are added up: of those that begin with a product, and so leave one literal
+    to an instruction (a second one costs two moves), the one whose partial
+    sums are rounded the least between 300 K and 3500 K."""
+    ts = [300.0 + 8.0 * i for i in range(401)]
+    term = {"E": lambda T: -rx["Ea"] / (R_J * T), "b": lambda T: rx["b"] * math.log(T),
+            "A": lambda T: math.log(rx["A"])}
+
+    def err(order):
+        return sum(math.ulp(sum(term[t](T) for t in order[:i])) ** 2
+                   for T in ts for i in range(1, len(order) + 1))
+    orders = [[t for t in o if t == "A" or (rx["Ea"] if t == "E" else rx["b"]) != 0.0]
+              for o in ("bEA", "EbA", "EAb", "bAE")]
+    return "".join(min(orders, key=err))
+
+
+def _activity_lines(m: dict, forms: list, unit=EXP_SCALE * LOG2E, ln="lgT",
+                    inverse=lambda k: f"ex(-g{k})") -> list:
     """Rates of progress in the form of _activity_form and their accumulation
-    into w_k, in the fewest instructions (the per-lane kernels are bound by
-    issue).  The exponent of k_f prod Ei_k is formed as a whole, one
-    exponential and no reciprocals, with the species' part shared by the
-    reactions of the same reactants, and in an order that leaves one literal to
-    an instruction (a second one costs two moves); a rate of progress goes into
-    the w_k by one fused operation a species, without being formed itself.
-    Against k_f times reciprocals of the E_k and rates added to the w_k, with
-    the stage update in one path (9 species; 1,150 -> 950 vector instructions a
-    stage): 4.2 M stiff cells 23.9 -> 22.2 ms, 96-box hierarchy 8.95 -> 8.2,
-    65,536 cells x 100 calls 8.7 -> 8.1.  Rounding error of a rate of progress,
-    rms, relative to its larger direction: 4e-15, as the sum of exponents of
-    either form (3e-15 to 4e-15)."""
-    L, sums = [], {}
+    into w_k.  The per-lane kernels are bound by issue, so the terms are shared
+    and ordered for the fewest instructions at the accuracy of k_f and k_r
+    formed each for itself: the Ei of a set of reactants serve all its reactions,
+    an instruction has one literal, and a rate of progress goes into the w_k by
+    one fused operation a species, without being formed itself.  ln k_f has an
+    exponential of its own: with the reactants' g_k/RT in the same exponent (a
+    sum of twice the size, no inverses; 4.2 M stiff cells 20.8 ms against 22.0)
+    the rates were off by twice as much.  Rounding error of a rate of progress, rms, relative to its
+    larger direction (9 species, 1e-15; k_f and k_r each for itself; g_k/RT in the
+    exponent): 300-1000 K 2.7 (2.7; 5.2), to 2000 K 2.6 (2.8; 4.8), to 3500 K 3.0
+    (3.2; 6.4).  unit, ln, inverse: what the exponents are in units of (here
+    ex(y) = 2^(y/EXP_SCALE)), the name of ln T in it and the text of Ei_k."""
+    def const(x):
+        return lit(float(Fraction(x) * unit))
+
+    L, sets = [], {}
+    for k in sorted({k for f in forms for k in f[0]}):
+        L.append(f"    const double i{k} = {inverse(k)};")
     for j, rx in enumerate(m["reactions"]):
         reac, prod, (fac, n) = forms[j]
-        G = "G" + "_".join(str(k) for k in reac)
-        if G not in sums:
-            sums[G] = " + ".join(f"g{k}" for k in reac)
-            L.append(f"    const double {G} = {sums[G]};")
-        y = G
-        if rx["Ea"] != 0.0:
-            y = f"({lit(_b2(-rx['Ea'] / R_J, EXP_SCALE))} * invT - {G})"
-        else:
-            y = f"(-{G})"
-        if rx["b"] != 0.0:
-            y = f"({lit(rx['b'])} * lgT + {y})"
+        P = "_".join(f"i{k}" for k in reac)
+        if len(reac) > 1 and P not in sets:
+            sets[P] = " * ".join(f"i{k}" for k in reac)
+            L.append(f"    const double {P} = {sets[P]};")
+        term = {"E": f"{const(-rx['Ea'] / R_J)} * invT", "b": f"{lit(rx['b'])} * {ln}",
+                "A": const(math.log(rx["A"]))}
+        order = _lkf_order(rx)
         L.append(f"    {{  // reaction {j}")
-        L.append(f"      const double K = ex({y} + {lit(EXP_SCALE * math.log2(rx['A']))});")
-        fw = " * ".join(f"a{k}" for k in reac)
-        rv = " * ".join([f"a{k}" for k in prod] + [fac] * n)
+        y = term[order[0]]
+        if len(order) > 1:
+            # (a statement of its own: the first product is rounded by itself)
+            L.append(f"      const double y0 = {y};")
+            y = "y0"
+        for t in order[1:]:
+            y = f"({y} + {term[t]})"
+        L.append(f"      const double K = ex({y});")
+        fw = " * ".join(f"c{k}" for k in reac)
+        rv = " * ".join([P] + [f"a{k}" for k in prod] + [fac] * n)
         if rx["tb"]:
             mt = " + ".join(f"{lit(a)} * c{k}" for k, a in enumerate(rx["eff"]))
             L.append(f"      const double d = ({mt}) * ({fw} - {rv});")
@@ -495,11 +495,11 @@ def _activity_lines(m: dict, forms: list) -> list:
 def gen_rhs(m: dict) -> str:
     sp = m["species"]
     N = len(sp)
-    base2 = N <= BASE2_MAX_N
+    conc = N <= CONC_MAX_N
     L = []
     L.append("  // f(u), u = (T, Y), for the full-storage and implicit schemes and the wide")
     L.append("  // mechanisms.")
-    L.append(f"  static constexpr bool BASE2 = {'true' if base2 else 'false'};")
+    L.append(f"  static constexpr bool CONC = {'true' if conc else 'false'};")
     L.append(f"  static constexpr double T_MIN = {lit(T_RATE_MIN)}, T_MAX = {lit(T_RATE_MAX)};")
     L.append("  __device__ __forceinline__ static void rhs(const double* __restrict__ u, double rho,")
     L.append("                                             double inv_rho, double* __restrict__ f) {")
@@ -507,7 +507,7 @@ def gen_rhs(m: dict) -> str:
     L.append("    // rho-dependent product (rho/W_k, third-body alpha_k rho/W_k, ...) is")
     L.append("    // hoisted out of the step loop and pinned in registers.")
     L.append("    asm volatile(\"\" : \"+v\"(rho), \"+v\"(inv_rho));")
-    if base2:
+    if conc:
         L.append("    double v[NS + 1];")
         L.append("    v[0] = u[0];")
         for k, s in enumerate(sp):
@@ -527,16 +527,15 @@ def gen_rhs(m: dict) -> str:
     else:
         L.append("    const double T = u[0];")
         L.append(f"    const double lnT = log_checked<Mech_{m['name']}_{m['hash']:016x}>(T, 1.0);")
-    forms = [_activity_form(m, rx) for rx in m["reactions"]] if base2 else [None]
+    forms = [_activity_form(m, rx) for rx in m["reactions"]] if conc else [None]
     activity = all(f is not None for f in forms)
-    scale = EXP_SCALE if activity else 1
-    L += _t_lines(m, scale)
+    L += _t_lines(m)
     for k, s in enumerate(sp):
-        L.append(f"    const double c{k} = v[{k + 1}];" if base2 else
+        L.append(f"    const double c{k} = v[{k + 1}];" if conc else
                  f"    const double c{k} = u[{k + 1}] * (rho * {lit(1.0 / s['W'])});")
     L.append("    double " + ", ".join(f"h{k}, g{k}" for k in range(N)) + ";")
     L.append("    double den = 0.0;  // sum_k c_k (cp_k/R - 1)")
-    L += _thermo(sp, scale)
+    L += _thermo(sp)
     L.append("    double " + ", ".join(f"w{k} = 0.0" for k in range(N)) + ";")
     inv = N <= FACTOR_INVERSES_MAX_N
     orders = [_reverse_factors(m, rx, inv) for rx in m["reactions"]]
@@ -547,22 +546,23 @@ def gen_rhs(m: dict) -> str:
         need = {f for o in orders if o for f in (o if inv else o[0] + o[1])}
     for k in range(N):
         if f"E{k}" in need or f"Ei{k}" in need:
-            L.append(f"    const double E{k} = {'ex' if activity else 'exp2_rate' if base2 else 'exp_ranged'}(g{k});")
+            L.append(f"    const double E{k} = {'ex' if activity else 'exp_ranged'}(g{k});")
         if f"Ei{k}" in need:
             L.append(f"    const double Ei{k} = rcp_nr(E{k});")
-        if activity and f"E{k}" in need:
+        if activity and any(k in f[1] for f in forms):
             L.append(f"    const double a{k} = c{k} * E{k};")
     C = m["pstd"] / R_CGS
     if "PRT" in need:
         L.append(f"    const double PRT = {lit(C)} * invT;")
     if "RTP" in need:
         L.append(f"    const double RTP = {lit(1.0 / C)} * T;")
-    L += _activity_lines(m, forms) if activity else _rate_lines(m, orders)
-    num = " + ".join(f"h{k} * w{k}" if base2 else f"(h{k} - 1.0) * w{k}" for k in range(N))
+    L += (_activity_lines(m, forms, unit=1, ln="lnT", inverse=lambda k: f"rcp_nr(E{k})") if activity
+          else _rate_lines(m, orders))
+    num = " + ".join(f"h{k} * w{k}" if conc else f"(h{k} - 1.0) * w{k}" for k in range(N))
     L.append(f"    const double num = {num};")
     L.append("    f[0] = -T * num * rcp_nr(den);")
     for k, s in enumerate(sp):
-        L.append(f"    f[{k + 1}] = w{k};" if base2 else
+        L.append(f"    f[{k + 1}] = w{k};" if conc else
                  f"    f[{k + 1}] = w{k} * ({lit(s['W'])} * inv_rho);")
     L.append("  }")
     return "\n".join(L)
@@ -803,7 +803,7 @@ def gen_coop(m: dict, tag: str) -> tuple[str, str]:
     """Tables of the cooperative (reaction-parallel) RHS.
 
     The same rate law as ``gen_rhs`` written as data: per reaction the three
-    Arrhenius coefficients of log2 k_f and of the T-only part of log2 k_r, the
+    Arrhenius coefficients of ln k_f and the factor (P/RT)^-dnu of k_r, the
     reactant and product species lists (a species of stoichiometric
     coefficient nu appears nu times; pad = N, whose concentration slot holds
     1), the net-stoichiometry terms of the K_c exponent (pad = N, g slot 0),
@@ -842,13 +842,12 @@ def gen_coop(m: dict, tag: str) -> tuple[str, str]:
         I.extend(int(x) for x in vals)
 
     dnu = [sum(v for _, v in n) for n in nets]
-    lg_p = Fraction(math.log2(m["pstd"] / R_CGS))
-    put_d("LNA", [math.log2(r["A"]) for r in rxs])
-    put_d("BEXP", [_b2(r["b"]) for r in rxs])
-    put_d("EAR", [_b2(r["Ea"] / R_J) for r in rxs])
-    # log2 of k_r's factor A (P/R)^-dnu and its exponent of T
-    put_d("LNAR", [float(Fraction(math.log2(r["A"])) - d * lg_p) for r, d in zip(rxs, dnu)])
-    put_d("BREV", [float((Fraction(r["b"]) + d) * LOG2E) for r, d in zip(rxs, dnu)])
+    put_d("LNA", [math.log(r["A"]) for r in rxs])
+    put_d("BEXP", [r["b"] for r in rxs])
+    put_d("EAR", [r["Ea"] / R_J for r in rxs])
+    # ln (P/RT)^-dnu = dnu ln T - dnu ln(P/R)
+    put_d("DNU", dnu)
+    put_d("LNPR", [-d * math.log(m["pstd"] / R_CGS) for d in dnu])
     gnu = []
     for n in nets:
         gnu += [float(v) for _, v in n] + [0.0] * (MG - len(n))
@@ -872,9 +871,8 @@ def gen_coop(m: dict, tag: str) -> tuple[str, str]:
         for s in sp:
             a = s[rng]
             row = [a[0] - 1.0, a[1] / 2, a[2] / 3, a[3] / 4, a[4] / 5, a[5],
-                   _b2(a[0]), _b2(a[1] / 2), _b2(a[2] / 6), _b2(a[3] / 12), _b2(a[4] / 20),
-                   _b2(a[5]), _b2(a[6]),
-                   a[0] - 1.0, a[1], a[2], a[3], a[4]]
+                   a[0], a[1] / 2, a[2] / 6, a[3] / 12, a[4] / 20, a[6],
+                   a[0] - 1.0, a[1], a[2], a[3], a[4], 0.0]
             assert len(row) == COOP_TH
             th += row
     put_d("TH", th)

@@ -41,7 +41,7 @@ __device__ __forceinline__ int advance(double (&u)[M::NS + 1], double rho, doubl
     const double err = take_step<M, S>(u, rho, inv_rho, hh, X, c, ex);
     double fac;
     if constexpr (S == SCHEME_RKF45) fac = step_factor_rkf(err);
-    else if constexpr (S == SCHEME_LSRK && M::BASE2) fac = step_factor_sq(err);
+    else if constexpr (S == SCHEME_LSRK && M::CONC) fac = step_factor_sq(err);
     else fac = step_factor(err);
     if (err <= 1.0) {
 #pragma unroll

@@ -49,7 +49,7 @@ namespace {
 // lanes (LB), in memory; else the polynomial.  The table's 32 KB are in every
 // block, so of blocks of 128 lanes three fit a CU, not four.
 template <class M, int LB, int S>
-using RateExp = std::conditional_t<!(M::BASE2 && S == SCHEME_LSRK), ExpPoly,
+using RateExp = std::conditional_t<!(M::CONC && S == SCHEME_LSRK), ExpPoly,
                                    std::conditional_t<LB == 64, ExpTable<const double*>,
                                                       ExpTable<lds_cdouble*>>>;
 template <class M, int LB, int S>
@@ -860,7 +860,7 @@ struct MechEntry {
 // Kernels are instantiated for launch bounds 256 (blocks of 64..256 threads)
 // and 512, and where the rates' table wants it for 64; the bound caps the registers the compiler may give a lane.
 template <class M, int S>
-constexpr int kSmallBlock = M::BASE2 && S == SCHEME_LSRK ? 64 : 256;
+constexpr int kSmallBlock = M::CONC && S == SCHEME_LSRK ? 64 : 256;
 
 template <class M, int S>
 hipError_t launch_direct_s(const PoolArgs& a, int block, hipStream_t s) {

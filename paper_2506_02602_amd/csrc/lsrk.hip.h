@@ -111,73 +111,70 @@ __device__ __forceinline__ double exp_cw(double x) {
 // 29.6 ms.
 __device__ __forceinline__ double exp_ranged(double x) { return exp_cw<true>(x); }
 
-constexpr double pow2(int k) { return k < 0 ? 0.5 * pow2(k + 1) : k > 0 ? 2.0 * pow2(k - 1) : 1.0; }
+// log2(e) in two parts.  The exponentials below reduce x to an integer m and f,
+// |f| <= 1/2, with e^x = 2^((m + f)/S): m = S x log2(e) rounded to the nearest
+// integer by adding and taking off 1.5 2^52 (m then also sits in the sum's low
+// word), f = S x log2(e) - m by two FMAs, whose first is all but exact.  The
+// exponents stay in base e, where the fits' coefficients are exact: with the
+// coefficients rounded to base 2, which spares these two FMAs one, rates were off
+// by 1.25 times as much.  For |m| < 2^31; NaN propagates through f.
+constexpr double LOG2E_HI = 0x1.71547652b82fep+0, LOG2E_LO = 0x1.777d0ffda0d24p-56;
 
-template <int BITS, int K>
-constexpr double exp_scale = pow2(-K * BITS);
-
-// 2^(y/2^BITS) for the rate constants of small mechanisms, whose exponents the
-// generated code forms in base 2: n = y/2^BITS rounded to the nearest integer
-// by adding and taking off 1.5 2^(52 + BITS) (n then also sits in the sum's low
-// word, for ldexp), f = y - n 2^BITS exact, and 2^(f/2^BITS) by a degree-11
-// polynomial in Horner form (interpolation of (2^f - 1)/f at the Chebyshev
-// nodes of |f| <= 1/2, coefficients rounded to doubles and scaled by powers of
-// two: relative error below 2e-17 in exact arithmetic, 0.8 ulp with the Horner
-// roundings).  For |n| < 2^31; NaN propagates through f.  15 VALU instructions
-// where exp_cw of the same rate takes 20 (its multiplication by 1/ln 2, clamp,
-// conversion and two-part reduction).
-template <int BITS>
-__device__ __forceinline__ double exp2_poly(double y) {
-  constexpr double D = 1.0 / (1 << BITS);
-  constexpr double MAGIC = 6755399441055744.0 / D;  // 1.5 2^52, in units of y
-  const double t = y + MAGIC;
-  const double f = y - (t - MAGIC);
-  double p = 0x1.e9d3fe3952179p-32 * exp_scale<BITS, 11>;
-  p = fma(p, f, 0x1.e6063f7217bc6p-28 * exp_scale<BITS, 10>);
-  p = fma(p, f, 0x1.b524fae627834p-24 * exp_scale<BITS, 9>);
-  p = fma(p, f, 0x1.62bfd47773353p-20 * exp_scale<BITS, 8>);
-  p = fma(p, f, 0x1.ffcbfc670dcd4p-17 * exp_scale<BITS, 7>);
-  p = fma(p, f, 0x1.430913096fd9fp-13 * exp_scale<BITS, 6>);
-  p = fma(p, f, 0x1.5d87fe78a5276p-10 * exp_scale<BITS, 5>);
-  p = fma(p, f, 0x1.3b2ab6fba1ddap-7 * exp_scale<BITS, 4>);
-  p = fma(p, f, 0x1.c6b08d704a0c2p-5 * exp_scale<BITS, 3>);
-  p = fma(p, f, 0x1.ebfbdff82c598p-3 * exp_scale<BITS, 2>);
-  p = fma(p, f, 0x1.62e42fefa39efp-1 * exp_scale<BITS, 1>);
+// 2^(m + f) by a degree-11 polynomial in Horner form (interpolation of (2^f -
+// 1)/f at the Chebyshev nodes of |f| <= 1/2, coefficients rounded to doubles:
+// relative error below 2e-17 in exact arithmetic, 0.8 ulp with the Horner
+// roundings).
+__device__ __forceinline__ double exp2_poly(double f, int m) {
+  double p = 0x1.e9d3fe3952179p-32;
+  p = fma(p, f, 0x1.e6063f7217bc6p-28);
+  p = fma(p, f, 0x1.b524fae627834p-24);
+  p = fma(p, f, 0x1.62bfd47773353p-20);
+  p = fma(p, f, 0x1.ffcbfc670dcd4p-17);
+  p = fma(p, f, 0x1.430913096fd9fp-13);
+  p = fma(p, f, 0x1.5d87fe78a5276p-10);
+  p = fma(p, f, 0x1.3b2ab6fba1ddap-7);
+  p = fma(p, f, 0x1.c6b08d704a0c2p-5);
+  p = fma(p, f, 0x1.ebfbdff82c598p-3);
+  p = fma(p, f, 0x1.62e42fefa39efp-1);
   p = fma(p, f, 1.0);
-  return ldexp(p, __double2loint(t));
+  return ldexp(p, m);
 }
 
-__device__ __forceinline__ double exp2_rate(double y) { return exp2_poly<0>(y); }
-
-// Exponentials of the activity form's exponents, 2^(y/4096).  ExpPoly: the
-// polynomial above, for kernels without the table.
+// Exponentials of the activity form.  ExpPoly: the polynomial above (S = 1),
+// for kernels without the table.
 struct ExpPoly {
-  __device__ __forceinline__ double operator()(double y) const { return exp2_poly<12>(y); }
+  __device__ __forceinline__ double operator()(double x) const {
+    constexpr double MAGIC = 6755399441055744.0;  // 1.5 2^52
+    const double t = fma(x, LOG2E_HI, MAGIC);
+    const double n = t - MAGIC;
+    const double f = fma(x, LOG2E_LO, fma(x, LOG2E_HI, -n));
+    return exp2_poly(f, __double2loint(t));
+  }
 };
 
 typedef const __attribute__((address_space(3))) double lds_cdouble;
 
-// ExpTable: m = y rounded to the nearest integer by adding and taking off 1.5
-// 2^52 (m also sits in the sum's low word), f = y - m exact, |f| <= 1/2, and
-// 2^(y/4096) = 2^(m >> 12) e (1 + p(f)) with e = 2^((m & 4095)/4096) from LDS
-// (correctly rounded) and p the degree-3 Taylor polynomial of 2^(f/4096) - 1
-// (truncation below 3e-18), e + e p rounded once: within 1.03 ulp.  For |y| <
-// 2^31; NaN propagates through f.  The per-lane kernels are bound by VALU issue,
-// and this takes 11 of those instructions and an LDS read where the polynomial
-// takes 15; 29 exponentials are in a stage of 9 species.  A smaller table needs
-// a term more (2,048 entries) or two, a larger one does not fit the LDS beside
-// the packing slots.  Against the polynomial: 4.2 M stiff cells 22.2 -> 20.8 ms,
-// 96-box hierarchy 8.2 -> 7.6, 65,536 cells x 100 calls 8.1 -> 7.5.
+// ExpTable (S = 4096): 2^((m + f)/4096) = 2^(m >> 12) e (1 + p(f)) with e =
+// 2^((m & 4095)/4096) from LDS (correctly rounded) and p the degree-3 Taylor
+// polynomial of 2^(f/4096) - 1 (truncation below 3e-18), e + e p rounded once:
+// within 1.03 ulp.  The per-lane kernels are bound by VALU issue, and this takes
+// 12 of those instructions and an LDS read where the polynomial takes 17; 30
+// exponentials are in a stage of 9 species.  A smaller table needs a term more
+// (2,048 entries) or two, a larger one does not fit the LDS beside the packing
+// slots.  Against the polynomial (both on exponents in base 2, one FMA less): 4.2
+// M stiff cells 22.2 -> 20.8 ms, 96-box hierarchy 8.2 -> 7.6, 65,536 cells x 100
+// calls 8.1 -> 7.5.
 // Blocks of 64 lanes read the table from memory instead (ExpTable<const
 // double*>, the same bits): in LDS it would leave room for three waves per CU.
 template <class P>
 struct ExpTable {
   P E;
-  __device__ __forceinline__ double operator()(double y) const {
+  __device__ __forceinline__ double operator()(double x) const {
     constexpr double MAGIC = 6755399441055744.0;  // 1.5 2^52
     constexpr double C1 = 0x1.62e42fefa39efp-1, C2 = 0x1.ebfbdff82c58fp-3, C3 = 0x1.c6b08d704a0c0p-5;
-    const double t = y + MAGIC;
-    const double f = y - (t - MAGIC);
+    const double t = fma(x, LOG2E_HI * 4096.0, MAGIC);
+    const double n = t - MAGIC;
+    const double f = fma(x, LOG2E_LO * 4096.0, fma(x, LOG2E_HI * 4096.0, -n));
     const int m = __double2loint(t);
     const double e = E[m & 4095];
     const double p = fma(f, fma(f, C3 * 0x1p-36, C2 * 0x1p-24), C1 * 0x1p-12);
@@ -208,7 +205,7 @@ static __constant__ double kExp2Frac[64] = {
 };
 
 // e^x from the 2^(j/64) table and a short polynomial (chem_eval_math; the
-// cooperative kernel takes exp2_tab below): m = 64 k + j is the integer nearest 64 x / ln 2 (clamped so the
+// cooperative kernel takes exp_coop below): m = 64 k + j is the integer nearest 64 x / ln 2 (clamped so the
 // conversion is defined), r = x - m ln2/64 by two FMAs with ln2/64 split in
 // two parts (|r| <= ln2/128), and e^x = 2^k 2^(j/64) (1 + p(r)) with p the
 // degree-6 Taylor polynomial of e^r - 1 (truncation below 3e-20 relative) by
@@ -235,33 +232,33 @@ __device__ __forceinline__ double exp_tab(double x, const double* E) {
   return ldexp(fma(t, p, t), mi >> 6);
 }
 
-// The literals of exp2_tab and log_near.  A wave alone on its SIMD spends 8
+// The literals of exp_coop and log_near.  A wave alone on its SIMD spends 8
 // cycles on each scalar move of a literal's half, so the cooperative kernel
 // loads them once (pin): into scalar registers, or vector registers where an
-// FMA has two of them.
+// FMA has two of them.  (c_k: ln2^k/k! in units of 1/64 octave.)
 struct NearConsts {
   double magic = 6755399441055744.0;  // 1.5 2^52
-  double c1 = 0x1.62e42fefa39efp-1, c2 = 0x1.ebfbdff82c58fp-3, c3 = 0x1.c6b08d704a0c0p-5;
-  double c4 = 0x1.3b2ab6fba4e77p-7, c5 = 0x1.5d87fe78a6731p-10, c6 = 0x1.430912f86c787p-13;
+  double c1 = 0x1.62e42fefa39efp-1 / 64, c2 = 0x1.ebfbdff82c58fp-3 / 4096;
+  double c3 = 0x1.c6b08d704a0c0p-5 / 262144, c4 = 0x1.3b2ab6fba4e77p-7 / 16777216;
+  double c5 = 0x1.5d87fe78a6731p-10 / 1073741824, c6 = 0x1.430912f86c787p-13 / 68719476736;
   double l3 = 1.0 / 3.0, l4 = -0.25, l5 = 1.0 / 5.0, l6 = -1.0 / 6.0, l7 = 1.0 / 7.0, l8 = -0.125;
+  double khi = LOG2E_HI * 64.0, klo = LOG2E_LO * 64.0;
   __device__ __forceinline__ void pin() {
-    asm volatile("" : "+s"(magic), "+s"(c1), "+s"(c3), "+s"(c5), "+s"(c6));
+    asm volatile("" : "+s"(magic), "+s"(c1), "+s"(c3), "+s"(c5), "+s"(c6), "+s"(klo));
     asm volatile("" : "+s"(l3), "+s"(l5), "+s"(l7), "+s"(l8));
-    asm volatile("" : "+v"(c2), "+v"(c4), "+v"(l4), "+v"(l6));
+    asm volatile("" : "+v"(khi), "+v"(c2), "+v"(c4), "+v"(l4), "+v"(l6));
   }
 };
 
-// 2^y for the cooperative kernel, whose exponents are in base 2: m = 64 y
-// rounded to the nearest integer by adding and taking off 1.5 2^52 (m also
-// sits in the sum's low word), f = y - m/64 exact, |f| <= 1/128, and 2^y =
-// 2^(m >> 6) 2^((m & 63)/64) (1 + p(f)) with p the degree-6 Taylor polynomial
-// of 2^f - 1 (truncation below 4e-20 relative), t + t p rounded once.  E
-// points at kExp2Frac's values (in LDS).  For |y| < 2^25; NaN propagates
-// through f.  Error as exp_tab's; three instructions and three steps of the
+// e^x for the cooperative kernel (S = 64, see LOG2E_HI): 2^((m + f)/64) = 2^(m
+// >> 6) 2^((m & 63)/64) (1 + p(f)) with p the degree-6 Taylor polynomial of
+// 2^(f/64) - 1 (truncation below 4e-20 relative), t + t p rounded once.  E
+// points at kExp2Frac's values (in LDS).  Error as exp_tab's, two steps of the
 // dependent chain shorter.
-__device__ __forceinline__ double exp2_tab(double y, const double* E, const NearConsts& k) {
-  const double t = fma(y, 64.0, k.magic);
-  const double f = fma(t - k.magic, -0.015625, y);
+__device__ __forceinline__ double exp_coop(double x, const double* E, const NearConsts& k) {
+  const double t = fma(x, k.khi, k.magic);
+  const double n = t - k.magic;
+  const double f = fma(x, k.klo, fma(x, k.khi, -n));
   const int m = __double2loint(t);
   const double e = E[m & 63];
   const double f2 = f * f;
@@ -321,7 +318,7 @@ __device__ __forceinline__ double log_atanh(double x) {
 }
 
 // ln T, NaN outside (T_MIN, T_MAX): there (far outside the fits) a rate
-// exponent could leave the range exp2_rate and exp2_tab take, and a NaN
+// exponent could leave the range ExpTable and exp_coop take, and a NaN
 // right-hand side is a rejected step.
 template <class M>
 __device__ __forceinline__ double log_checked(double T, double margin) {
@@ -377,8 +374,8 @@ __device__ __forceinline__ double step_factor_sq(double s) {
 }
 
 // One LSRK step of size h from u; X receives the new state, returns the WRMS
-// error (its square where M::BASE2, see step_factor_sq).  The per-lane kernels
-// are bound by instruction issue, so small mechanisms (M::BASE2) step
+// error (its square where M::CONC, see step_factor_sq).  The per-lane kernels
+// are bound by instruction issue, so small mechanisms (M::CONC) step
 // concentrations in place of mass fractions (rho is constant: no conversion in
 // the five right-hand sides), continue ln T of a stage from the step's start,
 // and take the norm with reciprocals in place of divisions (with the rates of
@@ -395,7 +392,7 @@ __device__ __forceinline__ double lsrk_step(const double (&u)[M::NS + 1], double
 #pragma unroll
   for (int i = 0; i < N1; ++i) { X[i] = u[i]; E[i] = 0.0; }
   [[maybe_unused]] double ln0, r0;
-  if constexpr (M::BASE2) {
+  if constexpr (M::CONC) {
     // (hide rho's invariance: its products would be kept in registers over
     // all steps, and from here to the norm)
     asm volatile("" : "+v"(rho), "+v"(inv_rho));
@@ -408,7 +405,7 @@ __device__ __forceinline__ double lsrk_step(const double (&u)[M::NS + 1], double
   for (int i = 0; i < N1; ++i) U[i] = X[i];
 #pragma unroll 1
   for (int s = 0; s < 5; ++s) {
-    if constexpr (M::BASE2) M::rhs_c(U, log_near<M>(U[0], u[0], ln0, r0, NearConsts{}), F, ex);
+    if constexpr (M::CONC) M::rhs_c(U, log_near<M>(U[0], u[0], ln0, r0, NearConsts{}), F, ex);
     else M::rhs(U, rho, inv_rho, F);
     const double bs = kStage[s].b, as = kStage[s].a, eh = kStage[s].e * h;
     // (the last stage has a = 0: its U is X; a branch of its own would cost
@@ -422,13 +419,13 @@ __device__ __forceinline__ double lsrk_step(const double (&u)[M::NS + 1], double
       X[i] = U[i] + bah * F[i];
     }
   }
-  if constexpr (M::BASE2) asm volatile("" : "+v"(rho), "+v"(inv_rho));
+  if constexpr (M::CONC) asm volatile("" : "+v"(rho), "+v"(inv_rho));
   double sum = 0.0;
 #pragma unroll
   for (int i = 0; i < N1; ++i) {
     const double sc = c.rtol * fabs(u[i]) + c.atol;
     double w;
-    if constexpr (M::BASE2) {
+    if constexpr (M::CONC) {
       double to_y = 1.0;
       if (i > 0) {
         to_y = M::W[i - 1] * inv_rho;
@@ -443,7 +440,7 @@ __device__ __forceinline__ double lsrk_step(const double (&u)[M::NS + 1], double
     }
     sum += w * w;
   }
-  return M::BASE2 ? sum * (1.0 / N1) : sqrt(sum * (1.0 / N1));
+  return M::CONC ? sum * (1.0 / N1) : sqrt(sum * (1.0 / N1));
 }
 
 template <int N1>

@@ -8,10 +8,9 @@
 // What bounds it: latency.  A wave is often alone on its SIMD, where a
 // dependent FP64 operation takes 9.5 cycles (independent ones 5), a scalar
 // move of a literal 8 and an LDS round trip 70-130, so the step is kept short
-// in dependent operations: ln T of a stage from the step's start (log_near),
-// exponents in base 2 with the T-only part of k_r's formed beside k_f's,
-// thermo rows in registers, sums in several chains, the controller's factor
-// from reciprocal square roots.  A lone wave's step of the 9-species mechanism
+// in dependent operations: ln T of a stage from the step's start (log_near), the
+// T-only part of k_r's exponent formed beside k_f's, thermo rows in registers,
+// sums in several chains, the controller's factor from reciprocal square roots.  A lone wave's step of the 9-species mechanism
 // takes 4.2 us (4.5 with the literals loaded where they are used, 5.3 without
 // any of these), about 200 instructions a stage; the 1024 x 1024 front 1.69 ->
 // 1.39 ms.
@@ -101,7 +100,7 @@ struct CoopLane {
   using C = typename M::Coop;
   static constexpr int R = (C::J + G - 1) / G;
   static constexpr bool PRE = R == 1 && C::L <= 16 && M::NS <= 16;
-  double lna, bexp, ear, lnar, brev;
+  double lna, bexp, ear, dnu, lnpr;
   double gnu[PRE ? C::MG : 1];
   int gk[PRE ? C::MG : 1], ri[PRE ? C::MR : 1], pi[PRE ? C::MR : 1];
   int tb;
@@ -129,8 +128,8 @@ struct CoopLane {
       lna = D[C::O_LNA + j];
       bexp = D[C::O_BEXP + j];
       ear = D[C::O_EAR + j];
-      lnar = D[C::O_LNAR + j];
-      brev = D[C::O_BREV + j];
+      dnu = D[C::O_DNU + j];
+      lnpr = D[C::O_LNPR + j];
 #pragma unroll
       for (int q = 0; q < C::MG; ++q) {
         gnu[q] = D[C::O_GNU + j * C::MG + q];
@@ -189,8 +188,8 @@ __device__ __forceinline__ double coop_rhs(double Yk, double T, double lnT, doub
   const double* th = PRE ? ln.th : D + C::O_TH + (lo ? 0 : N * C::TH_ROW) + k * C::TH_ROW;
   const double T2 = T * T;
   const double gp = fma(T2, fma(th[10], T, th[9]), fma(th[8], T, th[7]));
-  const double gk = fma(th[6], omlnT, fma(th[11], invT, -th[12])) - T * gp;
-  const double dk = c * fma(T2, fma(th[17], T2, fma(th[16], T, th[15])), fma(th[14], T, th[13]));
+  const double gk = fma(th[6], omlnT, fma(th[5], invT, -th[11])) - T * gp;
+  const double dk = c * fma(T2, fma(th[16], T2, fma(th[15], T, th[14])), fma(th[13], T, th[12]));
   {
     // lanes past N store into their own discard slot: no branch
     const int o = sl ? k : S::SX - S::SC + gl;
@@ -217,10 +216,10 @@ __device__ __forceinline__ double coop_rhs(double Yk, double T, double lnT, doub
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int j = min(gl + r * G, C::J - 1);
-    const double ea = (PRE ? ln.ear : D[C::O_EAR + j]) * invT;
-    kf[r] = exp2_tab((PRE ? ln.lna : D[C::O_LNA + j]) + (PRE ? ln.bexp : D[C::O_BEXP + j]) * lnT - ea,
-                     x.E, x.k);
-    lkr[r] = (PRE ? ln.lnar : D[C::O_LNAR + j]) + (PRE ? ln.brev : D[C::O_BREV + j]) * lnT - ea;
+    const double lkf = fma(PRE ? ln.bexp : D[C::O_BEXP + j], lnT,
+                           fma(PRE ? -ln.ear : -D[C::O_EAR + j], invT, PRE ? ln.lna : D[C::O_LNA + j]));
+    kf[r] = exp_coop(lkf, x.E, x.k);
+    lkr[r] = lkf + fma(PRE ? ln.dnu : D[C::O_DNU + j], lnT, PRE ? ln.lnpr : D[C::O_LNPR + j]);
   }
   const double hm1 = fma(T2, fma(th[4], T2, fma(th[3], T, th[2])), fma(th[1], T, th[0])) + th[5] * invT;
   // reactions: reverse rates, rates of progress
@@ -230,7 +229,7 @@ __device__ __forceinline__ double coop_rhs(double Yk, double T, double lnT, doub
     const int j0 = gl + r * G;
     const int j = min(j0, C::J - 1);
     // two chains over the reaction's net stoichiometry
-    double dg0 = lkr[r], dg1 = 0.0, cf, cr;
+    double dg0 = 0.0, dg1 = 0.0, cf, cr;
     if constexpr (PRE) {
 #pragma unroll
       for (int q = 0; q < C::MG; ++q) {
@@ -255,7 +254,7 @@ __device__ __forceinline__ double coop_rhs(double Yk, double T, double lnT, doub
         cr *= s[S::SC + I[C::O_PI + j * C::MR + q]];
       }
     }
-    const double kr = exp2_tab(dg0 + dg1, x.E, x.k);
+    const double kr = exp_coop(lkr[r] + (dg0 + dg1), x.E, x.k);
     // [M], or 1 + 0 without a third body
     const int row = PRE ? 0 : I[C::O_TB + j];
     double mt0 = PRE ? ln.one : D[C::O_TBONE + j], mt1 = 0.0;
