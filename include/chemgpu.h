@@ -486,13 +486,29 @@ int chem_eval_exp(const double *x, double *y, int64_t n, void *stream);
  *                         finite x > 0, NaN otherwise);
  *   CHEM_MATH_EXP_TAB     an exponential from a table of 2^(j/64) in LDS and a
  *                         degree-6 polynomial, about 1 ulp at most on [-745,
- *                         709] (the cooperative kernel takes 2^y from the same
- *                         table).
- * (1 is not used.)  CHEM_EINVAL for an unknown fn, n < 0 or a null array with
- * n > 0. */
+ *                         709] (no integrator calls it: CHEM_MATH_EXP_COOP);
+ *   CHEM_MATH_EXP_RANGED  EXP_CW's bits for |x| < 2^30, in fewer instructions:
+ *                         the rates of mechanisms above 16 species;
+ *   CHEM_MATH_EXP_POLY    the rates of the full-storage and implicit schemes of
+ *                         smaller mechanisms (a degree-11 polynomial of 2^f;
+ *                         |x| < 2^30, about 1.2 ulp at most);
+ *   CHEM_MATH_EXP_TABLE, CHEM_MATH_EXP_TABLE_MEM  the rates of smaller
+ *                         mechanisms in the low-storage scheme, one cell per
+ *                         lane (a table of 2^(j/4096) in LDS, or in memory for
+ *                         blocks of 64, with the same bits; |x| < 2^18, 1.03
+ *                         ulp at most);
+ *   CHEM_MATH_EXP_COOP    the cooperative kernel's rates (EXP_TAB's table; |x| <
+ *                         2^24, about 1 ulp at most).
+ * (1 and 7 are not used.)  CHEM_EINVAL for an unknown fn, n < 0 or a null array
+ * with n > 0. */
 #define CHEM_MATH_EXP_CW 0
 #define CHEM_MATH_LOG_ATANH 2
 #define CHEM_MATH_EXP_TAB 3
+#define CHEM_MATH_EXP_RANGED 4
+#define CHEM_MATH_EXP_POLY 5
+#define CHEM_MATH_EXP_TABLE 6
+#define CHEM_MATH_EXP_TABLE_MEM 8
+#define CHEM_MATH_EXP_COOP 9
 int chem_eval_math(int32_t fn, const double *x, double *y, int64_t n, void *stream);
 
 #ifdef __cplusplus

@@ -530,12 +530,13 @@ def chem_eval_exp(x, stream=None):
 
 _lib.chem_eval_math.restype = C.c_int
 _lib.chem_eval_math.argtypes = [C.c_int32, _P, _P, C.c_int64, _P]
-MATH_FNS = {"exp_cw": 0, "log_atanh": 2, "exp_tab": 3}
+MATH_FNS = {"exp_cw": 0, "log_atanh": 2, "exp_tab": 3, "exp_ranged": 4, "exp_poly": 5,
+            "exp_table": 6, "exp_table_mem": 8, "exp_coop": 9}
 
 
 def chem_eval_math(fn, x, stream=None):
     """fn(x) on the device with one of the integrators' own elementary
-    functions ("exp_cw", "log_atanh", "exp_tab")."""
+    functions (a key of MATH_FNS)."""
     import torch
     y = torch.empty_like(x)
     _check(_lib.chem_eval_math(MATH_FNS[fn], x.data_ptr(), y.data_ptr(), x.numel(),

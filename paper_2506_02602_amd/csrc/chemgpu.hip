@@ -126,14 +126,26 @@ struct Slots {
 
 __global__ void eval_math_kernel(int fn, const double* x, double* y, int64_t n) {
   __shared__ double E[64];  // exp_tab's table, staged in LDS as in the cooperative kernel
+  __shared__ double T[4096];  // ExpTable's
   for (int k = threadIdx.x; k < 64; k += blockDim.x) E[k] = kExp2Frac[k];
+  if (fn == CHEM_MATH_EXP_TABLE)
+    for (int k = threadIdx.x; k < 4096; k += blockDim.x) T[k] = kExp2Table[k];
   __syncthreads();
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const double v = x[i];
-  y[i] = fn == CHEM_MATH_LOG_ATANH ? log_atanh(v)
-         : fn == CHEM_MATH_EXP_TAB   ? exp_tab(v, E)
-                                     : exp_cw(v);
+  double r;
+  switch (fn) {
+    case CHEM_MATH_LOG_ATANH: r = log_atanh(v); break;
+    case CHEM_MATH_EXP_TAB: r = exp_tab(v, E); break;
+    case CHEM_MATH_EXP_RANGED: r = exp_ranged(v); break;
+    case CHEM_MATH_EXP_POLY: r = ExpPoly{}(v); break;
+    case CHEM_MATH_EXP_TABLE: r = ExpTable<lds_cdouble*>{(lds_cdouble*)T}(v); break;
+    case CHEM_MATH_EXP_TABLE_MEM: r = ExpTable<const double*>{kExp2Table}(v); break;
+    case CHEM_MATH_EXP_COOP: r = exp_coop(v, E, NearConsts{}); break;
+    default: r = exp_cw(v);
+  }
+  y[i] = r;
 }
 
 __global__ void pool_reset(unsigned long long* next, unsigned int* tail_count,
@@ -1834,8 +1846,7 @@ const char* chem_strerror(int code) {
 const char* chem_last_error(void) { return g_err.c_str(); }
 
 int chem_eval_math(int32_t fn, const double* x, double* y, int64_t n, void* stream) {
-  if (fn != CHEM_MATH_EXP_CW && fn != CHEM_MATH_LOG_ATANH &&
-      fn != CHEM_MATH_EXP_TAB)
+  if (fn < 0 || fn > CHEM_MATH_EXP_COOP || fn == 1 || fn == 7)
     return fail(CHEM_EINVAL, "chem_eval_math: unknown function");
   if (n < 0 || (n > 0 && (!x || !y))) return fail(CHEM_EINVAL, "chem_eval_math: bad argument");
   if (n == 0) return CHEM_OK;

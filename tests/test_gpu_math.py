@@ -1,0 +1,64 @@
+"""The elementary functions that form the integrators' rates, run on the device
+through chem_eval_math against extended precision."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+LOG2E = np.log2(np.exp(np.longdouble(1)))
+
+
+@pytest.fixture(scope="module")
+def cg():
+    from paper_2506_02602_amd import chemgpu
+    return chemgpu
+
+
+def device(cg, fn, x):
+    import torch
+    return cg.chem_eval_math(fn, torch.from_numpy(np.ascontiguousarray(x)).cuda()).cpu().numpy()
+
+
+def ulps(y, ref):
+    return (np.abs(y.astype(np.longdouble) - ref) /
+            np.spacing(np.abs(ref).astype(np.float64))).astype(np.float64)
+
+
+def exponents(scale, seed):
+    """Exponents over the double range and where rates live, and around the
+    reduction's ties (x S log2(e) half-way between integers, S = scale)."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    ties = ((rng.integers(-700 * scale, 700 * scale, 200_000) + np.longdouble(0.5)) / (scale * LOG2E))
+    ties = ties.astype(np.float64)
+    return np.concatenate([rng.uniform(-708.0, 709.0, 1_000_000), rng.uniform(-90.0, 90.0, 1_000_000),
+                           rng.uniform(-0.02, 0.02, 200_000), np.nextafter(ties, 1e9), ties,
+                           np.nextafter(ties, -1e9), [0.0, 1.0, -1.0, 709.7, -708.0]])
+
+
+# Bounds, in ulp: exp_table half for the table's entry, half for the last
+# rounding, 0.02 for the truncation and 2^-12 for the polynomial's roundings;
+# exp_coop the same with 0.03 for the roundings of p (|p| < 2^-7.5, below 4 ulp of
+# p); exp_poly 0.85 for the polynomial and two roundings of f (half an ulp of 1/2
+# each, times ln 2: 0.35 ulp each of a result near 1); exp_ranged is exp_cw.
+@pytest.mark.parametrize("fn,scale,bound", [("exp_table", 4096, 1.03), ("exp_table_mem", 4096, 1.03),
+                                            ("exp_coop", 64, 1.03), ("exp_poly", 1, 1.55),
+                                            ("exp_ranged", 1, 1.0)])
+def test_rate_exponentials(cg, fn, scale, bound):
+    x = exponents(scale, 51)
+    u = ulps(device(cg, fn, x), np.exp(x.astype(np.longdouble)))
+    v = ulps(device(cg, "exp_cw", x), np.exp(x.astype(np.longdouble)))
+    print(f"[{fn}] max {u.max():.3f} rms {np.sqrt((u * u).mean()):.4f} ulp, exp_cw {v.max():.3f} "
+          f"{np.sqrt((v * v).mean()):.4f}", flush=True)
+    assert u.max() <= bound
+    # far past the double range, up to the documented limits, and NaN
+    big = 2.0 ** (18 if scale == 4096 else 24 if scale == 64 else 30) * (1 - 2.0 ** -30)
+    y = device(cg, fn, np.array([0.0, 710.0, 2000.0, big, -746.0, -2000.0, -big, np.nan]))
+    assert y[0] == 1.0 and (y[1:4] == np.inf).all() and (y[4:7] == 0.0).all() and np.isnan(y[7])
+
+
+def test_bits_shared_by_the_variants(cg):
+    """The table in memory gives the LDS table's bits, the ranged exponential
+    exp_cw's."""
+    x = np.concatenate([exponents(4096, 52), exponents(1, 53)])
+    assert np.array_equal(device(cg, "exp_table", x), device(cg, "exp_table_mem", x))
+    assert np.array_equal(device(cg, "exp_ranged", x), device(cg, "exp_cw", x))
