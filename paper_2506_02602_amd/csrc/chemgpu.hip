@@ -124,6 +124,8 @@ struct Slots {
   static_assert(bytes(64) == 64 * (ND * sizeof(double) + NI * sizeof(int)), "slot_bytes");
 };
 
+struct MathBounds { static constexpr double T_MIN = 1.0, T_MAX = 1e5; };
+
 __global__ void eval_math_kernel(int fn, const double* x, double* y, int64_t n) {
   __shared__ double E[64];  // exp_tab's table, staged in LDS as in the cooperative kernel
   __shared__ double T[4096];  // ExpTable's
@@ -135,6 +137,7 @@ __global__ void eval_math_kernel(int fn, const double* x, double* y, int64_t n) 
   if (i >= n) return;
   const double v = x[i];
   double r;
+  const double v0 = x[i & ~(int64_t)63];
   switch (fn) {
     case CHEM_MATH_LOG_ATANH: r = log_atanh(v); break;
     case CHEM_MATH_EXP_TAB: r = exp_tab(v, E); break;
@@ -143,6 +146,9 @@ __global__ void eval_math_kernel(int fn, const double* x, double* y, int64_t n) 
     case CHEM_MATH_EXP_TABLE: r = ExpTable<lds_cdouble*>{(lds_cdouble*)T}(v); break;
     case CHEM_MATH_EXP_TABLE_MEM: r = ExpTable<const double*>{kExp2Table}(v); break;
     case CHEM_MATH_EXP_COOP: r = exp_coop(v, E, NearConsts{}); break;
+    case CHEM_MATH_LOG_NEAR:
+      r = log_near<MathBounds>(v, v0, log_checked_parts<MathBounds>(v0, 1.02), rcp_nr(v0), NearConsts{});
+      break;
     default: r = exp_cw(v);
   }
   y[i] = r;
@@ -1846,7 +1852,7 @@ const char* chem_strerror(int code) {
 const char* chem_last_error(void) { return g_err.c_str(); }
 
 int chem_eval_math(int32_t fn, const double* x, double* y, int64_t n, void* stream) {
-  if (fn < 0 || fn > CHEM_MATH_EXP_COOP || fn == 1 || fn == 7)
+  if (fn < 0 || fn > CHEM_MATH_LOG_NEAR || fn == 1 || fn == 7)
     return fail(CHEM_EINVAL, "chem_eval_math: unknown function");
   if (n < 0 || (n > 0 && (!x || !y))) return fail(CHEM_EINVAL, "chem_eval_math: bad argument");
   if (n == 0) return CHEM_OK;

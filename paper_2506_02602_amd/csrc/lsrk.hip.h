@@ -290,7 +290,9 @@ __device__ __forceinline__ double rcp_nr(double x) {
 // harmless.  Within 1 ulp of the correctly rounded logarithm; about a third of
 // the library logarithm's instructions and dependency depth, which carries
 // double-double intermediates for correct rounding.
-__device__ __forceinline__ double log_atanh(double x) {
+struct LogParts { double hi, lo; };  // a logarithm and what its last rounding left off
+
+__device__ __forceinline__ LogParts log_atanh_parts(double x) {
   constexpr double LN2_HI = 0.6931471803691238;     // ln 2, low 21 mantissa bits cleared
   constexpr double LN2_LO = 1.9082149292705877e-10;  // ln 2 - LN2_HI
   constexpr double SQRT_HALF = 0.70710678118654752;
@@ -313,33 +315,45 @@ __device__ __forceinline__ double log_atanh(double x) {
   const double q = fma(a4, z8, fma(fma(a3, z2, a2), z4, fma(a1, z2, a0)));
   const double hfsq = 0.5 * f * f;
   const double de = (double)e;
-  const double y = de * LN2_HI - ((hfsq - fma(s, fma(z, q, hfsq), de * LN2_LO)) - f);
-  return x > 0.0 ? y : __builtin_nan("");
+  // (|b| <= 0.36, so next to |a| or a = 0: lo is the sum's exact remainder)
+  const double a = de * LN2_HI;
+  const double b = (hfsq - fma(s, fma(z, q, hfsq), de * LN2_LO)) - f;
+  const double y = a - b;
+  return {x > 0.0 ? y : __builtin_nan(""), (a - y) - b};
 }
+
+__device__ __forceinline__ double log_atanh(double x) { return log_atanh_parts(x).hi; }
 
 // ln T, NaN outside (T_MIN, T_MAX): there (far outside the fits) a rate
 // exponent could leave the range ExpTable and exp_coop take, and a NaN
 // right-hand side is a rejected step.
 template <class M>
-__device__ __forceinline__ double log_checked(double T, double margin) {
-  const double y = log_atanh(T);
-  return T > M::T_MIN * margin && T * margin < M::T_MAX ? y : __builtin_nan("");
+__device__ __forceinline__ LogParts log_checked_parts(double T, double margin) {
+  LogParts y = log_atanh_parts(T);
+  if (!(T > M::T_MIN * margin && T * margin < M::T_MAX)) y.hi = __builtin_nan("");
+  return y;
 }
 
-// ln T of a stage from that of the step's start, ln0 = log_checked(T0, 1.02):
-// ln T = ln T0 + ln(1 + d), d = (T - T0)/T0, by the Taylor series to d^8 for
-// |d| <= 2^-6 (truncation below 2^-57, absolute).  A lane further off gets
+template <class M>
+__device__ __forceinline__ double log_checked(double T, double margin) {
+  return log_checked_parts<M>(T, margin).hi;
+}
+
+// ln T of a stage from that of the step's start, ln0 = log_checked_parts(T0,
+// 1.02): ln T = ln T0 + ln(1 + d), d = (T - T0)/T0, by the Taylor series to d^8
+// for |d| <= 2^-6 (truncation below 2^-57, absolute); ln T0's remainder goes
+// into d, so the sum is rounded once like ln T itself.  A lane further off gets
 // log_checked, whatever the other lanes of its wave hold; one that is not
 // stays within 1.6 % of T0, so within the range T0 was checked for.
 template <class M>
-__device__ __forceinline__ double log_near(double T, double T0, double ln0, double r0,
+__device__ __forceinline__ double log_near(double T, double T0, const LogParts& ln0, double r0,
                                            const NearConsts& k) {
-  const double d = (T - T0) * r0;
+  const double d = fma(T - T0, r0, ln0.lo);
   const double d2 = d * d, d4 = d2 * d2;
   const double a = fma(d, k.l3, -0.5), b = fma(d, k.l5, k.l4);
   const double c = fma(d, k.l7, k.l6);
   const double q = fma(fma(d2, k.l8, c), d4, fma(b, d2, a));
-  double y = ln0 + fma(d2, q, d);
+  double y = ln0.hi + fma(d2, q, d);
   const bool far = !(fabs(d) <= 0x1p-6);
   if (__builtin_expect(__any(far), 0)) {
     const double full = log_checked<M>(T, 1.0);
@@ -391,14 +405,15 @@ __device__ __forceinline__ double lsrk_step(const double (&u)[M::NS + 1], double
   double U[N1], E[N1], F[N1];
 #pragma unroll
   for (int i = 0; i < N1; ++i) { X[i] = u[i]; E[i] = 0.0; }
-  [[maybe_unused]] double ln0, r0;
+  [[maybe_unused]] LogParts ln0;
+  [[maybe_unused]] double r0;
   if constexpr (M::CONC) {
     // (hide rho's invariance: its products would be kept in registers over
     // all steps, and from here to the norm)
     asm volatile("" : "+v"(rho), "+v"(inv_rho));
 #pragma unroll
     for (int i = 1; i < N1; ++i) X[i] = u[i] * (rho * M::INVW[i - 1]);
-    ln0 = log_checked<M>(u[0], 1.02);
+    ln0 = log_checked_parts<M>(u[0], 1.02);
     r0 = rcp_nr(u[0]);
   }
 #pragma unroll

@@ -293,14 +293,18 @@ __device__ __forceinline__ double coop_step(double uT, double uk, double rho, do
                                             const CoopCtx<M>& x, CoopLane<M, G>& ln) {
   using S = CoopScratch<M>;
   constexpr int N = M::NS, N1 = N + 1;
-  const double ln0 = log_checked<M>(uT, 1.02), r0 = rcp_nr(uT);
+  // (ready here: the compiler would form the remainder where the stages use it,
+  // a lone step 4 % longer)
+  LogParts ln0 = log_checked_parts<M>(uT, 1.02);
+  asm volatile("" : "+v"(ln0.hi), "+v"(ln0.lo));
+  const double r0 = rcp_nr(uT);
   double UT = uT, Uk = uk, ET = 0.0, Ek = 0.0;
   XT = uT;
   Xk = uk;
   auto stage = [&](int s) {
     double FT;
-    const double Fk = coop_rhs<M, G>(Uk, UT, s == 0 ? ln0 : log_near<M>(UT, uT, ln0, r0, x.k), rho, inv_rho,
-                                     x, ln, FT);
+    const double Fk = coop_rhs<M, G>(Uk, UT, s == 0 ? ln0.hi : log_near<M>(UT, uT, ln0, r0, x.k),
+                                     rho, inv_rho, x, ln, FT);
     const double bs = s == 0 ? LS_B[0] : s == 1 ? LS_B[1] : s == 2 ? LS_B[2] : s == 3 ? LS_B[3] : LS_B[4];
     const double bhs = s == 0 ? LS_BH[0] : s == 1 ? LS_BH[1] : s == 2 ? LS_BH[2] : s == 3 ? LS_BH[3] : LS_BH[4];
     const double as = s == 0 ? LS_A[0] : s == 1 ? LS_A[1] : s == 2 ? LS_A[2] : s == 3 ? LS_A[3] : 0.0;

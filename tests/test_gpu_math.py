@@ -62,3 +62,31 @@ def test_bits_shared_by_the_variants(cg):
     x = np.concatenate([exponents(4096, 52), exponents(1, 53)])
     assert np.array_equal(device(cg, "exp_table", x), device(cg, "exp_table_mem", x))
     assert np.array_equal(device(cg, "exp_ranged", x), device(cg, "exp_cw", x))
+
+
+def test_log_near(cg):
+    """ln T continued from the step's start: at most 1 ulp off, as the logarithm
+    it stands for (0.5 for its one rounding; the start's remainder and the
+    series are off by some 5e-17, 0.13 of the smallest ulp here; past |d| = 2^-6
+    the full logarithm, within 1), on either side of the switch and where ln T changes its binade; NaN
+    where the start or the value is out of range."""
+    rng = np.random.Generator(np.random.PCG64(54))
+    T0 = np.concatenate([rng.uniform(200.0, 5000.0, 20000), np.exp(8.0) + rng.uniform(-60, 60, 4000),
+                         rng.uniform(1.1, 90000.0, 8000)])
+    d = np.concatenate([rng.uniform(-1.0, 1.0, 40) * 2.0 ** -6, rng.uniform(-1.0, 1.0, 15) * 2.0 ** -12,
+                        [0.0, 2.0 ** -6, -2.0 ** -6, 0.0157, -0.0157, 0.02, -0.3, 0.05]])
+    x = np.concatenate([T0[:, None], T0[:, None] * (1.0 + d[None])], axis=1)
+    assert x.shape[1] == 64
+    near = np.abs(x / x[:, :1] - 1.0) < 2.0 ** -6 - 1e-12
+    y = device(cg, "log_near", x.reshape(-1)).reshape(x.shape)
+    ok = (x > 1.03) & (x < 97000.0)
+    u = np.where(ok, ulps(y, np.log(x.astype(np.longdouble))), 0.0)
+    v = np.where(ok, ulps(device(cg, "log_atanh", x.reshape(-1)).reshape(x.shape),
+                          np.log(x.astype(np.longdouble))), 0.0)
+    print(f"[log_near] max {u[near].max():.3f} rms {np.sqrt((u[near] ** 2).mean()):.4f} ulp, far "
+          f"{u[~near].max():.3f}; log_atanh {v.max():.3f} {np.sqrt((v[near] ** 2).mean()):.4f}", flush=True)
+    hot = near & (x > 20.0)                # (near 1 the result's ulp is below the start's)
+    assert u[hot].max() <= 0.63 and u[~near].max() <= 1.0
+    bad = np.array([[0.9] * 64, [2e5] * 64, [np.nan] * 64, [500.0] * 63 + [np.nan]])
+    y = device(cg, "log_near", bad.reshape(-1)).reshape(bad.shape)
+    assert np.isnan(y[:3]).all() and np.isnan(y[3, 63]) and not np.isnan(y[3, :63]).any()
