@@ -501,7 +501,9 @@ int chem_eval_exp(const double *x, double *y, int64_t n, void *stream);
  *                         2^24, about 1 ulp at most);
  *   CHEM_MATH_LOG_NEAR    ln T of a step's stages, continued from that of its
  *                         start: here ln x[i] from that of x[64 (i / 64)] (both
- *                         in 1 to 1e5, NaN otherwise; 1 ulp at most).
+ *                         in 1 to 1e5, NaN otherwise; 1 ulp at most);
+ *   CHEM_MATH_STEP_FACTOR the controller's step factor 0.9 x^(-1/8) within [1/5,
+ *                         5] of the squared error norm x (3 ulp at most).
  * (1 and 7 are not used.)  CHEM_EINVAL for an unknown fn, n < 0 or a null array
  * with n > 0. */
 #define CHEM_MATH_EXP_CW 0
@@ -513,6 +515,7 @@ int chem_eval_exp(const double *x, double *y, int64_t n, void *stream);
 #define CHEM_MATH_EXP_TABLE_MEM 8
 #define CHEM_MATH_EXP_COOP 9
 #define CHEM_MATH_LOG_NEAR 10
+#define CHEM_MATH_STEP_FACTOR 11
 int chem_eval_math(int32_t fn, const double *x, double *y, int64_t n, void *stream);
 
 #ifdef __cplusplus

@@ -149,6 +149,7 @@ __global__ void eval_math_kernel(int fn, const double* x, double* y, int64_t n) 
     case CHEM_MATH_LOG_NEAR:
       r = log_near<MathBounds>(v, v0, log_checked_parts<MathBounds>(v0, 1.02), rcp_nr(v0), NearConsts{});
       break;
+    case CHEM_MATH_STEP_FACTOR: r = step_factor_sq(v); break;
     default: r = exp_cw(v);
   }
   y[i] = r;
@@ -1852,7 +1853,7 @@ const char* chem_strerror(int code) {
 const char* chem_last_error(void) { return g_err.c_str(); }
 
 int chem_eval_math(int32_t fn, const double* x, double* y, int64_t n, void* stream) {
-  if (fn < 0 || fn > CHEM_MATH_LOG_NEAR || fn == 1 || fn == 7)
+  if (fn < 0 || fn > CHEM_MATH_STEP_FACTOR || fn == 1 || fn == 7)
     return fail(CHEM_EINVAL, "chem_eval_math: unknown function");
   if (n < 0 || (n > 0 && (!x || !y))) return fail(CHEM_EINVAL, "chem_eval_math: bad argument");
   if (n == 0) return CHEM_OK;

@@ -374,15 +374,17 @@ __device__ __forceinline__ double step_factor(double err) {
 }
 
 // The same factor from the squared norm s = err^2, 0.9 s^(-1/8): three
-// hardware reciprocal square roots, 1/sqrt(1/sqrt(1/sqrt(s))), and one Newton
-// step y + y (1 - s y^8)/8, which squares their relative error (2^-22 or so);
-// a third of the dependent chain of two square roots and a division.
+// hardware reciprocal square roots, 1/sqrt(1/sqrt(1/sqrt(s))), whose relative
+// error (some 2^-22) one step of third order, y (1 + r/8 + 9/128 r^2) with r = 1
+// - s y^8, takes below 2^-60: 0.49 ulp rms, 2.1 at most (square roots and a
+// division: 0.62, 2.4), in a third of their dependent chain.
 __device__ __forceinline__ double step_factor_sq(double s) {
   if (!(s < 1e7)) return 0.2;        // also NaN and infinity
   if (s < 1e-7) return 5.0;
   double y = __builtin_amdgcn_rsq(__builtin_amdgcn_rsq(__builtin_amdgcn_rsq(s)));
   const double y2 = y * y, y4 = y2 * y2;
-  y = fma(0.125 * y, fma(-s, y4 * y4, 1.0), y);
+  const double r = fma(-s, y4 * y4, 1.0);
+  y = fma(y * r, fma(9.0 / 128.0, r, 0.125), y);
   const double fac = 0.9 * y;
   return fac < 0.2 ? 0.2 : fac > 5.0 ? 5.0 : fac;
 }

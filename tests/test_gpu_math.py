@@ -90,3 +90,23 @@ def test_log_near(cg):
     bad = np.array([[0.9] * 64, [2e5] * 64, [np.nan] * 64, [500.0] * 63 + [np.nan]])
     y = device(cg, "log_near", bad.reshape(-1)).reshape(bad.shape)
     assert np.isnan(y[:3]).all() and np.isnan(y[3, 63]) and not np.isnan(y[3, :63]).any()
+
+
+def test_step_factor(cg):
+    """0.9 x^(-1/8) of the squared norm x, within [0.2, 5]: no further off than the
+    square roots and the division it stands for, at most and in the mean; exact
+    at the clamps and for 0, infinity and NaN."""
+    rng = np.random.Generator(np.random.PCG64(55))
+    x = np.concatenate([10.0 ** rng.uniform(-6.0, 5.3, 1_000_000), rng.uniform(0.5, 2.0, 1_000_000), [1.0]])
+    y = device(cg, "step_factor", x)
+    ref = np.longdouble(0.9) * x.astype(np.longdouble) ** np.longdouble(-0.125)
+    in_range = (ref > 0.2000001) & (ref < 4.999999)
+    u = ulps(y[in_range], ref[in_range])
+    e = np.sqrt(x)                          # the same from the norm itself
+    v = ulps(0.9 * (1.0 / np.sqrt(np.sqrt(e))), ref)[in_range]
+    print(f"[step_factor] max {u.max():.3f} rms {np.sqrt((u * u).mean()):.4f} ulp, square roots "
+          f"{v.max():.3f} {np.sqrt((v * v).mean()):.4f}", flush=True)
+    assert in_range.sum() > 1_900_000 and y[-1] == 0.9
+    assert u.max() <= v.max() and (u * u).mean() <= (v * v).mean()
+    y = device(cg, "step_factor", np.array([0.0, 1e-300, 1e-8, 1e8, 1e300, np.inf, np.nan]))
+    assert (y[:3] == 5.0).all() and (y[3:] == 0.2).all()
