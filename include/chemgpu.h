@@ -122,6 +122,14 @@ typedef struct {
  *   v = N+2      h    step-size hint [s]        in (<= 0 or >= dt: start with dt) /
  *                                               out (controller's next proposal)
  * with ld >= n_cells.  The caller owns the memory.
+ *
+ * T: rates exist between 0.5 K and 1e5 K (fixed at build time per mechanism,
+ * narrower only where its exponents would leave the exponential's range
+ * there).  A step that evaluates them outside is rejected and retried smaller,
+ * so a cell that starts outside ends with CHEM_CELL_H_UNDERFLOW, as does one so
+ * far outside its NASA-7 fits that a rate overflows (for the built-in
+ * mechanisms below 40 K with 9 species and 75 K with 32, and above 20,000 K to
+ * 50,000 K).
  */
 
 /* Load a mechanism from a .mech text file and bind the kernel that was

@@ -208,7 +208,7 @@ def _thermo(species):
     return L
 
 
-# Temperatures outside which the right-hand side is made NaN (see _t_lines).
+# Widest window of temperatures of a right-hand side (see _t_window).
 T_RATE_MIN, T_RATE_MAX = 0.5, 1e5
 # Lowest temperature for which the factorised reverse rates are range-checked.
 T_FACTOR_MIN = 200.0
@@ -359,22 +359,34 @@ def _rate_lines(m: dict, orders: list) -> list:
     return L
 
 
-def _t_lines(m: dict) -> list:
-    """What the rates and the thermo need of T beside ln T: 1/T, 1 - ln T,
-    powers.  Outside (T_RATE_MIN, T_RATE_MAX) the device's ln T is NaN
-    (log_checked): there (far outside the fits) an exponent could leave the
-    range ExpTable and exp_coop take (2^19 and 2^25 octaves), and a NaN
-    right-hand side is a rejected step (the factors of the reverse rates leave
-    the double range far above T_RATE_MIN)."""
-    for T in (T_RATE_MIN, T_RATE_MAX):
+def _t_window(m: dict) -> tuple:
+    """Temperatures between which the right-hand side is evaluated: the widest of
+    T_RATE_MIN 2^i to T_RATE_MAX 2^-j within which every exponent stays in the
+    range that ExpTable and exp_coop take (2^19 and 2^25 octaves).  Far outside
+    the fits either way: the factors of the reverse rates leave the double range
+    at some 40 K and 50,000 K."""
+    octaves = 2.0 ** 31 / EXP_SCALE if len(m["species"]) <= CONC_MAX_N else 2.0 ** 25
+
+    def fits(T):
         g = [abs(_g_rt(sp, T)) for sp in m["species"]]
         # k_f's with the species' terms of either side (or one species' alone)
         big = g + [abs(math.log(rx["A"])) + abs(rx["b"] * math.log(T)) + abs(rx["Ea"]) / R_J / T +
                    sum(v * g[k] for side in ("reac", "prod") for k, v in rx[side].items())
                    for rx in m["reactions"]]
-        octaves = 2.0 ** 31 / EXP_SCALE if len(m["species"]) <= CONC_MAX_N else 2.0 ** 25
-        if max(big) > octaves * math.log(2.0):
-            raise ValueError(f"{m['name']}: rate exponents at {T} K leave the range of the exponential")
+        return max(big) <= octaves * math.log(2.0)
+    lo = [T for T in (T_RATE_MIN * 2.0 ** i for i in range(7)) if fits(T)]
+    hi = [T for T in (T_RATE_MAX * 0.5 ** j for j in range(4)) if fits(T)]
+    if not lo or not hi:
+        raise ValueError(f"{m['name']}: rate exponents leave the range of the exponential "
+                         f"at {T_RATE_MIN * 64} K or at {T_RATE_MAX / 8} K")
+    return lo[0], hi[0]
+
+
+def _t_lines(m: dict) -> list:
+    """What the rates and the thermo need of T beside ln T: 1/T, 1 - ln T,
+    powers.  Outside _t_window the device's ln T is NaN (log_checked), and a NaN
+    right-hand side is a rejected step."""
+    _t_window(m)
     return ["    const double invT = rcp_nr(T);",
             "    const double omlnT = 1.0 - lnT;",
             "    const double T2 = T * T, T3 = T2 * T, T4 = T2 * T2;",
@@ -500,7 +512,8 @@ def gen_rhs(m: dict) -> str:
     L.append("  // f(u), u = (T, Y), for the full-storage and implicit schemes and the wide")
     L.append("  // mechanisms.")
     L.append(f"  static constexpr bool CONC = {'true' if conc else 'false'};")
-    L.append(f"  static constexpr double T_MIN = {lit(T_RATE_MIN)}, T_MAX = {lit(T_RATE_MAX)};")
+    t_min, t_max = _t_window(m)
+    L.append(f"  static constexpr double T_MIN = {lit(t_min)}, T_MAX = {lit(t_max)};")
     L.append("  __device__ __forceinline__ static void rhs(const double* __restrict__ u, double rho,")
     L.append("                                             double inv_rho, double* __restrict__ f) {")
     L.append("    // Hide rho's loop invariance from the optimiser: otherwise every")
