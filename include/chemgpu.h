@@ -92,8 +92,8 @@ typedef struct {
                             and run with block_size <= 256 (CHEM_EINVAL otherwise) */
     int32_t tail_cap;    /* most handed-over cells per CU that the cooperative kernel takes
                             (see tail_steps): > 0 = that many, < 0 = no limit, 0 = the
-                            tuned value, else whatever their number if it is expected to
-                            finish them first */
+                            value tuned with tail_steps (if that is 0 too), else whatever
+                            their number if it is expected to finish them first */
     int32_t pool_order;  /* 1: before the step, cells expected to take many steps (a step
                             hint below dt/8 over the flow step, or without a usable hint
                             T >= 1000 K) are dealt round-robin over the first work claim of
@@ -294,28 +294,31 @@ void chem_graph_destroy(chem_graph g);
 
 /*
  * Autotune block size, chunk length and cooperative hand-off for these
- * boxes by coordinate descent: chunk in {1, 2, 4, 8, 16, 32, 64} at the
- * default block, then, when the best of those calls took under 50 ms,
+ * boxes: the launch of a call that names none of them, then, by coordinate
+ * descent, chunk in {1, 2, 4, 8, 16, 32, 64} at the default block, then, when the best of those calls took under 50 ms,
  * every pair of block in {64, 128, 192, 256, 384, 512} (those that fit the
  * LDS compaction slots) and chunk, otherwise block at the best chunk and
  * chunk again at the best block; then, if base->tail_steps is 0, tail_steps in {4, 8, 16, 32, 64,
  * 128, 256, 512, never} for the best pair, and, if base->tail_cap is 0 too,
- * the pairs of tail_steps in {4, 8, 16, 32, 64} and tail_cap in {64, 128,
- * 256, no limit}, then, if base->pool_order is 0, each of the three pool orders,
+ * the pairs of tail_steps in {4, 8, 16, 32, 64} and tail_cap in {0, 64, 128,
+ * 256, no limit}, then, if base->pool_order is 0, each of the pool orders,
  * then block and chunk once more at the final hand-off, cap and order (the
  * whole plane when calls take under 50 ms, else chunk, block, chunk).  Each candidate is timed with HIP
  * events on `stream` (median of `reps` launches after one untimed launch);
  * the eight fastest distinct launches are then timed again, round-robin,
- * 3 * reps + 1 launches each, and the lowest median wins (2 * reps + 2
+ * 3 * reps + 1 launches each, the default launch among them, and the lowest
+ * median wins, the default's if none is lower by more than 1 % (2 * reps + 2
  * untimed launches come first, so start-up clocks do not count).  Trials run on the
  * caller's boxes; the boxes' states are snapshotted first and restored
  * after every trial and at the end, so the caller's data is left unchanged.  The
  * winner is stored in the handle for the size bucket of these boxes (total
- * cells rounded to a power of two): later calls whose chunk_steps,
- * block_size, tail_steps or tail_cap are 0 use it.  If cache_path
+ * cells rounded up to a power of two; pools small enough for the cooperative
+ * kernel alone apart from larger ones): later calls whose chunk_steps,
+ * block_size, tail_steps, tail_cap or pool_order are 0 use it.  If cache_path
  * is not NULL the result is also looked up in / written to that JSON file,
- * keyed by mechanism hash, size bucket and GPU architecture name; a cache hit
- * skips the sweep.  best (may be NULL) receives the chosen options.
+ * keyed by mechanism hash, size bucket, GPU architecture name and a revision of
+ * the kernels (entries of another are left as they are and tuned anew); a cache
+ * hit skips the sweep.  best (may be NULL) receives the chosen options.
  * Allocates the snapshots (and, on a miss, grows the workspace reservation to
  * the boxes' cells if it is smaller); synchronises `stream`.
  */
@@ -435,7 +438,7 @@ int surrogate_infer(chem_surr s, chem_mech m, double *state, int64_t ld, int64_t
  * sit scattered in the block, in the order the list was built).  The
  * block is restored after every trial and on return.  `base` gives rtol,
  * atol, max_steps and the scheme, and any launch field it fixes.  A cache
- * entry (key hash:size-bucket:arch:surrogate, file as for chem_autotune)
+ * entry (keyed as for chem_autotune with ":surrogate" at the end, same file)
  * is returned without tuning; otherwise the result is appended to it.  The
  * result goes to *best only (the mechanism's tuned table is for plain
  * integrations).  A set-up call: reserves what the trials need, allocates a

@@ -1130,7 +1130,7 @@ struct chem_mech_s {
   TailStore tail;
   OrderStore order;
   struct Tuned { int block, chunk, tail, cap, order; };
-  std::map<int, Tuned> tuned;  // (size bucket, scheme) -> tuned launch
+  std::map<int, Tuned> tuned;  // (size bucket, direct size or not, scheme) -> tuned launch
   // workspace, all of it allocated by chem_workspace_reserve
   unsigned long long* d_next = nullptr;
   BoxDesc* d_boxes = nullptr;      // kBoxRing slots of kMaxBoxes entries
@@ -1266,8 +1266,6 @@ int check_scheme_launch(chem_mech m, const chem_opts* o, int block) {
 
 constexpr int kDefaultBlock = 128;
 constexpr int kDefaultChunk = 8;
-constexpr int kDefaultTail = 32;
-constexpr int kDefaultTailCap = 64;
 
 int size_bucket(int64_t total) {
   int b = 0;
@@ -1275,9 +1273,15 @@ int size_bucket(int64_t total) {
   return b;
 }
 
-// Tuned launches are kept per (size bucket, scheme).
-int tuned_key(int64_t total, const chem_opts* o) {
-  return size_bucket(total) * 4 + (o ? o->scheme : SCHEME_LSRK);
+// Pools that the cooperative kernel takes as they are, if nothing says otherwise.
+bool direct_size(chem_mech m, int64_t total, const chem_opts* o) {
+  return total <= m->coop_slots && (!o || (o->scheme == SCHEME_LSRK && o->fixed_steps == 0));
+}
+
+// Tuned launches are kept per size bucket and scheme, those of direct sizes
+// apart (the bucket that their limit falls into holds both).
+int tuned_key(chem_mech m, int64_t total, const chem_opts* o) {
+  return (size_bucket(total) * 2 + direct_size(m, total, o)) * 4 + (o ? o->scheme : SCHEME_LSRK);
 }
 
 // How a call is launched.  direct: its cells go to the cooperative kernel as
@@ -1309,7 +1313,7 @@ struct Launch { bool direct; int block, chunk, tail, cap, order; float auto_coop
 Launch size_launch(chem_mech m, int64_t total) {
   const bool wide = m->entry->coop_groups == 1;  // a whole wave per cell
   Launch l{};
-  l.direct = total <= m->coop_slots;
+  l.direct = direct_size(m, total, nullptr);
   l.block = size_block(m->entry->ns, wide);
   l.chunk = wide ? 2 : 1;
   l.tail = wide ? 8 : 4;
@@ -1344,9 +1348,10 @@ Launch pick_launch(chem_mech m, int64_t total, const chem_opts* o) {
     }
     if (tail || cap) l.direct = false;
   };
-  auto it = m->tuned.find(tuned_key(total, o));
-  if (it != m->tuned.end())
-    take(it->second.block, it->second.chunk, it->second.tail, it->second.cap, it->second.order);
+  auto it = m->tuned.find(tuned_key(m, total, o));
+  if (it != m->tuned.end())  // (its cap was found with its hand-off)
+    take(it->second.block, it->second.chunk, it->second.tail, o && o->tail_steps ? 0 : it->second.cap,
+         it->second.order);
   if (o) take(o->block_size, o->chunk_steps, o->tail_steps, o->tail_cap, o->pool_order);
   return l;
 }
@@ -1541,6 +1546,23 @@ std::string arch_name(int device) {
 
 struct TuneEntry { std::string key; int block, chunk, tail, cap, order; double ms; };
 
+// A cache entry's key: mechanism, size, device, revision of the kernels and their
+// launches (raised when either changes enough to move the choices; entries of
+// another are left alone and tuned anew), scheme and kind of call.
+constexpr int kLaunchRev = 2;
+
+std::string cache_key(chem_mech m, int64_t total, const chem_opts* o, const char* kind) {
+  char key[200];
+  snprintf(key, sizeof key, "%016llx:%d:%s:v%d%s%s%s", (unsigned long long)m->entry->hash,
+           size_bucket(total), arch_name(m->device).c_str(), kLaunchRev,
+           direct_size(m, total, o) ? ":direct" : "",
+           (o && o->scheme == SCHEME_RKF45)  ? ":rkf45"
+           : (o && o->scheme == SCHEME_ROS4) ? ":ros4"
+                                             : "",
+           kind);
+  return key;
+}
+
 std::vector<TuneEntry> read_cache(const char* path) {
   std::vector<TuneEntry> v;
   FILE* f = fopen(path, "rb");
@@ -1594,10 +1616,12 @@ int write_cache(const char* path, const std::vector<TuneEntry>& v) {
 // The launch search shared by chem_autotune and surrogate_autotune.
 // time_one(t, &ms) runs one call with launch t (from the caller's pristine
 // data) and times it.  Fills the best launch of the search into `best`
-// (launch fields only) and its median time into *best_ms.
+// (launch fields only) and its median time into *best_ms.  The launch of a call
+// of `total` cells that names none of its fields is timed with the others, in
+// every round, and is the answer unless another is faster by more than 1 %.
 using TimeOne = std::function<int(const chem_opts&, float*)>;
 
-int tune_search(chem_mech m, const chem_opts& o, int reps, const TimeOne& time_one,
+int tune_search(chem_mech m, const chem_opts& o, int64_t total, int reps, const TimeOne& time_one,
                 chem_opts* best, double* best_ms_out) {
   int rc;
   // median time of `reps` calls of one configuration (after one untimed call)
@@ -1613,11 +1637,11 @@ int tune_search(chem_mech m, const chem_opts& o, int reps, const TimeOne& time_o
     *med = ms[ms.size() / 2];
     return CHEM_OK;
   };
-  // Coordinate descent: chunk at the default block, block at the best
-  // chunk, chunk again at the best block, then the hand-off point for the
+  // The default launch, then coordinate descent: chunk at the default block,
+  // block at the best chunk, chunk again at the best block, then the hand-off point for the
   // best pair, then hand-off point and cooperative cap together (an early
   // hand-off only pays when the cap lets the cooperative kernel take the
-  // longer list), then the two pool orders, then block and chunk once more
+  // longer list), then the other pool orders, then block and chunk once more
   // at the final hand-off, cap and order.  Each sweep keeps the incumbent
   // unless a candidate is faster.  Then the fastest few launches seen are
   // timed again, round-robin and with more calls each, so that one noisy
@@ -1631,12 +1655,19 @@ int tune_search(chem_mech m, const chem_opts& o, int reps, const TimeOne& time_o
   constexpr double kTuneGridMs = 50.0;
   struct Seen { int b, c, tl, cap, ord; double ms; };
   std::vector<Seen> seen;
-  const int caps[] = {kDefaultTailCap, 128, 256, -1};
+  auto same = [](const Seen& x, const Seen& y) {
+    return x.b == y.b && x.c == y.c && x.tl == y.tl && x.cap == y.cap && x.ord == y.ord;
+  };
+  const int caps[] = {0, 64, 128, 256, -1};  // (0: the estimate decides)
   double best_ms = 1e300;
-  int best_block = kDefaultBlock, best_chunk = kDefaultChunk;
-  int best_tail = o.tail_steps != 0 ? o.tail_steps : kDefaultTail;
-  int best_cap = o.tail_cap != 0 ? o.tail_cap : kDefaultTailCap;
-  int best_order = o.pool_order != 0 ? o.pool_order : -1;
+  chem_opts unnamed = o;
+  unnamed.block_size = unnamed.chunk_steps = 0;
+  const Launch d = pick_launch(m, total, &unnamed);
+  int best_block = d.block, best_chunk = d.chunk;
+  int best_tail = o.tail_steps != 0 ? o.tail_steps : d.direct ? 0 : d.tail;
+  int best_cap = o.tail_cap;
+  int best_order = o.pool_order != 0 ? o.pool_order : d.order != 0 ? d.order : -1;
+  const Seen def{best_block, best_chunk, best_tail, best_cap, best_order, 0.0};
   const bool tune_tail = o.tail_steps == 0 && o.fixed_steps == 0 && o.scheme == SCHEME_LSRK;
   const bool tune_cap = tune_tail && o.tail_cap == 0;
   auto consider = [&](int b, int c, int tl, int cap, int ord) -> int {
@@ -1671,6 +1702,13 @@ int tune_search(chem_mech m, const chem_opts& o, int reps, const TimeOne& time_o
       rc = time_one(t, &el);
     }
   }
+  if (rc == CHEM_OK) rc = consider(def.b, def.c, def.tl, def.cap, def.ord);
+  if (d.direct) {
+    // no other field counts in that launch: the sweeps start from the size
+    // rule's hand-off
+    best_ms = 1e300;
+    best_tail = size_launch(m, total).tail;
+  }
   for (int c : chunks)
     if (rc == CHEM_OK) rc = consider(best_block, c, best_tail, best_cap, o0);
   if (rc == CHEM_OK && best_ms < kTuneGridMs) {
@@ -1699,9 +1737,9 @@ int tune_search(chem_mech m, const chem_opts& o, int reps, const TimeOne& time_o
         if (rc == CHEM_OK && !(tl == t0 && cap == k0)) rc = consider(b0, c0, tl, cap, o0);
   }
   if (o.pool_order == 0 && o.fixed_steps == 0) {
-    // the three pool orders at the best launch so far
-    if (rc == CHEM_OK) rc = consider(best_block, best_chunk, best_tail, best_cap, ORDER_DEAL);
-    if (rc == CHEM_OK) rc = consider(best_block, best_chunk, best_tail, best_cap, ORDER_RANGE);
+    // the other pool orders at the best launch so far
+    for (int ord : {-1, (int)ORDER_DEAL, (int)ORDER_RANGE})
+      if (rc == CHEM_OK && ord != o0) rc = consider(best_block, best_chunk, best_tail, best_cap, ord);
     if (rc == CHEM_OK && best_tail > 0)
       rc = consider(best_block, best_chunk, best_tail, best_cap, ORDER_RANGE_DEFER);
   }
@@ -1736,11 +1774,13 @@ int tune_search(chem_mech m, const chem_opts& o, int reps, const TimeOne& time_o
     std::vector<Seen> top;
     for (const Seen& v : seen) {
       bool dup = false;
-      for (const Seen& w : top)
-        dup = dup || (w.b == v.b && w.c == v.c && w.tl == v.tl && w.cap == v.cap && w.ord == v.ord);
+      for (const Seen& w : top) dup = dup || same(w, v);
       if (!dup) top.push_back(v);
       if (top.size() == 8) break;
     }
+    bool has_def = false;
+    for (const Seen& w : top) has_def = has_def || same(w, def);
+    if (!has_def) top.push_back(def);
     std::vector<std::vector<float>> ms(top.size());
     for (int r = 0; r < 3 * reps + 1 && rc == CHEM_OK; ++r)
       for (size_t k = 0; k < top.size() && rc == CHEM_OK; ++k) {
@@ -1785,9 +1825,10 @@ int tune_search(chem_mech m, const chem_opts& o, int reps, const TimeOne& time_o
       auto add = [&](int b, int c, int tl, int cap, int ord) {
         if (!block_fits(m->entry->ns, b)) return;
         if (o.scheme == SCHEME_ROS4 && b > 256) return;
+        const Seen v{b, c, tl, cap, ord, 0.0};
         for (const Seen& w : cand)
-          if (w.b == b && w.c == c && w.tl == tl && w.cap == cap && w.ord == ord) return;
-        cand.push_back({b, c, tl, cap, ord, 0.0});
+          if (same(w, v)) return;
+        cand.push_back(v);
       };
       const int ib = at(blocks, NB, cur.b), ic = at(chunks, NC, cur.c), it = at(tails, NT, cur.tl);
       for (int d : {-1, 1}) {
@@ -1800,6 +1841,7 @@ int tune_search(chem_mech m, const chem_opts& o, int reps, const TimeOne& time_o
         for (int k = 0; k < NK; ++k) add(cur.b, cur.c, cur.tl, caps[k], cur.ord);
       if (o.pool_order == 0 && o.fixed_steps == 0)
         for (int ord : orders) add(cur.b, cur.c, cur.tl, cur.cap, ord);
+      add(def.b, def.c, def.tl, def.cap, def.ord);
       if (cand.size() < 2) break;
       std::vector<std::vector<float>> ms(cand.size());
       for (int r = 0; r < 3 * reps + 1 && rc == CHEM_OK; ++r)
@@ -1820,6 +1862,11 @@ int tune_search(chem_mech m, const chem_opts& o, int reps, const TimeOne& time_o
         if (med < win_ms) { win_ms = med; win = k; }
       }
       best_ms = win_ms;
+      for (size_t k = 0; k < cand.size(); ++k)
+        if (same(cand[k], def) && ms[k][ms[k].size() / 2] <= 1.01 * win_ms) {
+          win = k;
+          best_ms = ms[k][ms[k].size() / 2];
+        }
       if (win == 0) break;
       best_block = cand[win].b; best_chunk = cand[win].c; best_tail = cand[win].tl;
       best_cap = cand[win].cap; best_order = cand[win].ord;
@@ -2280,14 +2327,8 @@ int chem_autotune(chem_mech m, const chem_box* boxes, int32_t n_boxes, const che
   if (total == 0) return fail(CHEM_EINVAL, "chem_autotune: no cells");
   if (reps < 1) reps = 3;
   hipStream_t s = (hipStream_t)stream;
-  const int bucket = size_bucket(total);
-  const int tkey = tuned_key(total, base);
-  char key[160];
-  snprintf(key, sizeof key, "%016llx:%d:%s%s", (unsigned long long)m->entry->hash, bucket,
-           arch_name(m->device).c_str(),
-           (base && base->scheme == SCHEME_RKF45)  ? ":rkf45"
-           : (base && base->scheme == SCHEME_ROS4) ? ":ros4"
-                                                   : "");
+  const int tkey = tuned_key(m, total, base);
+  const std::string key = cache_key(m, total, base, "");
   chem_opts o = base ? *base : chem_opts{0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   std::vector<TuneEntry> cache;
   if (cache_path) {
@@ -2346,7 +2387,12 @@ int chem_autotune(chem_mech m, const chem_box* boxes, int32_t n_boxes, const che
   };
   chem_opts found{};
   double best_ms = 0.0;
-  rc = tune_search(m, o, reps, time_one, &found, &best_ms);
+  // (a launch tuned before is not the default to search from)
+  const auto old = m->tuned.find(tkey);
+  const chem_mech_s::Tuned kept = old != m->tuned.end() ? old->second : chem_mech_s::Tuned{};
+  const bool had = m->tuned.erase(tkey) > 0;
+  rc = tune_search(m, o, total, reps, time_one, &found, &best_ms);
+  if (rc != CHEM_OK && had) m->tuned[tkey] = kept;
   if ((e = restore()) != hipSuccess && rc == CHEM_OK) rc = hip_fail(e, "restore");
   if ((e = hipStreamSynchronize(s)) != hipSuccess && rc == CHEM_OK) rc = hip_fail(e, "autotune sync");
   (void)hipEventDestroy(e0);

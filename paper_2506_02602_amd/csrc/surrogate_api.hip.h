@@ -545,12 +545,7 @@ int surrogate_autotune(chem_surr s, chem_mech m, double* state, int64_t ld, int6
   if (rc) return rc;
   if (reps < 1) reps = 3;
   hipStream_t st = (hipStream_t)stream;
-  char key[180];
-  snprintf(key, sizeof key, "%016llx:%d:%s%s:surrogate", (unsigned long long)m->entry->hash,
-           size_bucket(n_cells), arch_name(m->device).c_str(),
-           (base && base->scheme == SCHEME_RKF45)  ? ":rkf45"
-           : (base && base->scheme == SCHEME_ROS4) ? ":ros4"
-                                                   : "");
+  const std::string key = cache_key(m, n_cells, base, ":surrogate");
   const chem_opts o = base ? *base : chem_opts{0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   std::vector<TuneEntry> cache;
   if (cache_path) {
@@ -604,7 +599,7 @@ int surrogate_autotune(chem_surr s, chem_mech m, double* state, int64_t ld, int6
   };
   chem_opts found{};
   double best_ms = 0.0;
-  rc = tune_search(m, o, reps, time_one, &found, &best_ms);
+  rc = tune_search(m, o, n_cells, reps, time_one, &found, &best_ms);
   if ((e = hipMemcpyAsync(state, snap, bytes, hipMemcpyDeviceToDevice, st)) != hipSuccess &&
       rc == CHEM_OK)
     rc = hip_fail(e, "restore");

@@ -50,3 +50,39 @@ def test_scheduling_fields_keep_the_bits(mech9_path, n, entry):
         got = run(**kw)
         assert torch.equal(ref[0], got[0]) and torch.equal(ref[1], got[1]), kw
     gm.close()
+
+
+@pytest.mark.parametrize("n", [64, 3000])
+def test_tuning_keeps_the_direct_launch(mech9_path, n):
+    """The autotuner times the launch of a call that names nothing: for a pool that
+    the cooperative kernel takes as it is (where everything else first steps the
+    cells one per lane, three times as long) that launch stays, for tuned calls
+    and with the options it returns, bit for bit; a larger pool of the same size
+    bucket does not change it."""
+    import torch
+    from paper_2506_02602_amd import chemgpu as cg
+    s0, hot = wl.front_2d(mech9_path, nx=1024, ny=1024, seed=94)
+    s = np.ascontiguousarray(s0[:, hot][:, :n])
+    gm = cg.chem_mech_load(mech9_path)
+    cg.chem_workspace_reserve(gm, 8000)
+
+    def run(opts=None):
+        st = to_gpu(s)
+        cg.chem_set_kernel_timing(gm, True)
+        cg.chem_integrate(gm, st, wl.DT_FLOW, opts)
+        torch.cuda.synchronize()
+        kt = cg.chem_kernel_times(gm)
+        cg.chem_set_kernel_timing(gm, False)
+        return st, kt["coop"] > 10 * kt["persistent"]
+    ref, direct = run()
+    assert direct
+    best = cg.chem_autotune(gm, [dict(state=to_gpu(s), dt=wl.DT_FLOW)], reps=1)
+    for opts in (None, best):
+        got, direct = run(opts)
+        assert direct and torch.equal(got, ref)
+    if n > 2048:
+        big = np.ascontiguousarray(s0[:, hot][:, :8000])
+        cg.chem_autotune(gm, [dict(state=to_gpu(big), dt=wl.DT_FLOW)], reps=1)
+        s = np.ascontiguousarray(s0[:, hot][:, :4500])     # 4,097 to 8,192: the same bucket
+        assert run()[1]
+    gm.close()
