@@ -72,7 +72,8 @@ typedef struct {
     int32_t max_steps;   /* accepted + rejected steps per cell (default 100000) */
     int32_t chunk_steps; /* steps a lane takes between compaction points; 0 = default,
                             < 0 = no compaction (one cell per lane for the whole step) */
-    int32_t block_size;  /* threads per block, multiple of 64 up to 512 (0 = default) */
+    int32_t block_size;  /* threads per block, multiple of 64 up to 512 (0 = default; scheme 0
+                            on up to 16 species runs 64 as 128) */
     int32_t fixed_steps; /* > 0: test mode, exactly this many steps of dt/fixed_steps, no control */
     int32_t tail_steps;  /* a cell still stepping after this many steps (accepted + rejected,
                             over all sub-calls) is handed over; the cooperative kernel,
@@ -503,11 +504,9 @@ int chem_eval_exp(const double *x, double *y, int64_t n, void *stream);
  *   CHEM_MATH_EXP_POLY    the rates of the full-storage and implicit schemes of
  *                         smaller mechanisms (a degree-11 polynomial of 2^f;
  *                         |x| < 2^30, about 1.2 ulp at most);
- *   CHEM_MATH_EXP_TABLE, CHEM_MATH_EXP_TABLE_MEM  the rates of smaller
- *                         mechanisms in the low-storage scheme, one cell per
- *                         lane (a table of 2^(j/4096) in LDS, or in memory for
- *                         blocks of 64, with the same bits; |x| < 2^18, 1.03
- *                         ulp at most);
+ *   CHEM_MATH_EXP_TABLE   the rates of smaller mechanisms in the low-storage
+ *                         scheme, one cell per lane (a table of 2^(j/4096) in
+ *                         LDS; |x| < 2^18, 1.03 ulp at most);
  *   CHEM_MATH_EXP_COOP    the cooperative kernel's rates (EXP_TAB's table; |x| <
  *                         2^24, about 1 ulp at most);
  *   CHEM_MATH_LOG_NEAR    ln T of a step's stages, continued from that of its
@@ -515,15 +514,14 @@ int chem_eval_exp(const double *x, double *y, int64_t n, void *stream);
  *                         in 1 to 1e5, NaN otherwise; 1 ulp at most);
  *   CHEM_MATH_STEP_FACTOR the controller's step factor 0.9 x^(-1/8) within [1/5,
  *                         5] of the squared error norm x (3 ulp at most).
- * (1 and 7 are not used.)  CHEM_EINVAL for an unknown fn, n < 0 or a null array
- * with n > 0. */
+ * (1, 7 and 8 are not used.)  CHEM_EINVAL for an unknown fn, n < 0 or a null
+ * array with n > 0. */
 #define CHEM_MATH_EXP_CW 0
 #define CHEM_MATH_LOG_ATANH 2
 #define CHEM_MATH_EXP_TAB 3
 #define CHEM_MATH_EXP_RANGED 4
 #define CHEM_MATH_EXP_POLY 5
 #define CHEM_MATH_EXP_TABLE 6
-#define CHEM_MATH_EXP_TABLE_MEM 8
 #define CHEM_MATH_EXP_COOP 9
 #define CHEM_MATH_LOG_NEAR 10
 #define CHEM_MATH_STEP_FACTOR 11

@@ -531,7 +531,7 @@ def chem_eval_exp(x, stream=None):
 _lib.chem_eval_math.restype = C.c_int
 _lib.chem_eval_math.argtypes = [C.c_int32, _P, _P, C.c_int64, _P]
 MATH_FNS = {"exp_cw": 0, "log_atanh": 2, "exp_tab": 3, "exp_ranged": 4, "exp_poly": 5,
-            "exp_table": 6, "exp_table_mem": 8, "exp_coop": 9, "log_near": 10, "step_factor": 11}
+            "exp_table": 6, "exp_coop": 9, "log_near": 10, "step_factor": 11}
 
 
 def chem_eval_math(fn, x, stream=None):

@@ -45,26 +45,22 @@ using namespace chemgpu;
 namespace {
 
 // The exponential of a kernel's rates: the table where the scheme steps
-// concentrations, in the block's LDS (load_exp fills it) or, for blocks of 64
-// lanes (LB), in memory; else the polynomial.  The table's 32 KB are in every
-// block, so of blocks of 128 lanes three fit a CU, not four.
-template <class M, int LB, int S>
-using RateExp = std::conditional_t<!(M::CONC && S == SCHEME_LSRK), ExpPoly,
-                                   std::conditional_t<LB == 64, ExpTable<const double*>,
-                                                      ExpTable<lds_cdouble*>>>;
-template <class M, int LB, int S>
-constexpr int kTableLen = std::is_same_v<RateExp<M, LB, S>, ExpTable<lds_cdouble*>>
-                              ? sizeof(kExp2Table) / sizeof(double) : 1;
+// concentrations, in the block's LDS (load_exp fills it), else the polynomial.
+// The table's 32 KB are in every block, so of blocks of 128 lanes three fit a
+// CU, not four, and of 64 three would (kTableBlock).
+template <class M, int S>
+constexpr bool kRateTable = M::CONC && S == SCHEME_LSRK;
+template <class M, int S>
+using RateExp = std::conditional_t<kRateTable<M, S>, ExpTable, ExpPoly>;
+template <class M, int S>
+constexpr int kTableLen = kRateTable<M, S> ? sizeof(kExp2Table) / sizeof(double) : 1;
 
 // (Eight loads in flight a lane, so one latency for a block of 256; the caller
 // synchronises.)
-template <class M, int LB, int S>
-__device__ __forceinline__ RateExp<M, LB, S> load_exp(double* E) {
-  using Exp = RateExp<M, LB, S>;
-  if constexpr (std::is_same_v<Exp, ExpTable<const double*>>) {
-    return Exp{kExp2Table};
-  } else if constexpr (std::is_same_v<Exp, ExpTable<lds_cdouble*>>) {
-    constexpr int N2 = kTableLen<M, LB, S> / 2, U = 8;
+template <class M, int S>
+__device__ __forceinline__ RateExp<M, S> load_exp(double* E) {
+  if constexpr (kRateTable<M, S>) {
+    constexpr int N2 = kTableLen<M, S> / 2, U = 8;
     const double2* src = reinterpret_cast<const double2*>(kExp2Table);
     double2* dst = reinterpret_cast<double2*>(E);
     for (int j0 = threadIdx.x; j0 < N2; j0 += U * blockDim.x) {
@@ -77,9 +73,9 @@ __device__ __forceinline__ RateExp<M, LB, S> load_exp(double* E) {
         if (j < N2) dst[j] = v[k];
       }
     }
-    return Exp{(lds_cdouble*)E};
+    return ExpTable{(lds_cdouble*)E};
   } else {
-    return Exp{};
+    return ExpPoly{};
   }
 }
 
@@ -89,8 +85,8 @@ __global__ __launch_bounds__(LB) void lsrk_direct(PoolArgs a) {
   constexpr int N1 = M::NS + 1;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const BoxDesc& bd = a.one;
-  __shared__ __attribute__((aligned(16))) double sE[kTableLen<M, LB, S>];
-  const RateExp<M, LB, S> ex = load_exp<M, LB, S>(sE);
+  __shared__ __attribute__((aligned(16))) double sE[kTableLen<M, S>];
+  const RateExp<M, S> ex = load_exp<M, S>(sE);
   __syncthreads();
   if (i >= bd.n) return;
   double u[N1], rho, h;
@@ -143,8 +139,7 @@ __global__ void eval_math_kernel(int fn, const double* x, double* y, int64_t n) 
     case CHEM_MATH_EXP_TAB: r = exp_tab(v, E); break;
     case CHEM_MATH_EXP_RANGED: r = exp_ranged(v); break;
     case CHEM_MATH_EXP_POLY: r = ExpPoly{}(v); break;
-    case CHEM_MATH_EXP_TABLE: r = ExpTable<lds_cdouble*>{(lds_cdouble*)T}(v); break;
-    case CHEM_MATH_EXP_TABLE_MEM: r = ExpTable<const double*>{kExp2Table}(v); break;
+    case CHEM_MATH_EXP_TABLE: r = ExpTable{(lds_cdouble*)T}(v); break;
     case CHEM_MATH_EXP_COOP: r = exp_coop(v, E, NearConsts{}); break;
     case CHEM_MATH_LOG_NEAR:
       r = log_near<MathBounds>(v, v0, log_checked_parts<MathBounds>(v0, 1.02), rcp_nr(v0), NearConsts{});
@@ -523,10 +518,10 @@ __global__ __launch_bounds__(LB) void lsrk_persistent(PoolArgs a) {
   const float prio = a.resume ? resume_priority(a.tail.btot, (float)gridDim.x * (float)B) : 0.f;
 
   // claim the first B items
-  __shared__ __attribute__((aligned(16))) double sE[kTableLen<M, LB, S>];
+  __shared__ __attribute__((aligned(16))) double sE[kTableLen<M, S>];
   unsigned long long got = 0;
   if (tid == 0) got = atomicAdd(a.next, (unsigned long long)B);
-  const RateExp<M, LB, S> ex = total > 0 ? load_exp<M, LB, S>(sE) : RateExp<M, LB, S>{};
+  const RateExp<M, S> ex = total > 0 ? load_exp<M, S>(sE) : RateExp<M, S>{};
   if (tid == 0) {
     s_base = (long long)got;
     s_pack = 0;
@@ -691,16 +686,16 @@ __global__ __launch_bounds__(LB) void lsrk_persistent(PoolArgs a) {
           // time (one atomic per 64 cells), near it what it needs (no cell
           // waits behind a wave's long ones)
           const int batch = total - seen > 4 * lanes ? 64 : need - have;
-          unsigned long long got = 0;
-          if (lane == 0) got = atomicAdd(a.next, (unsigned long long)batch);
-          got = ((unsigned long long)(unsigned int)__builtin_amdgcn_readfirstlane((int)(got >> 32)) << 32) |
-                (unsigned int)__builtin_amdgcn_readfirstlane((int)got);
-          const int64_t left = total - (int64_t)got;
+          unsigned long long q = 0;
+          if (lane == 0) q = atomicAdd(a.next, (unsigned long long)batch);
+          q = ((unsigned long long)(unsigned int)__builtin_amdgcn_readfirstlane((int)(q >> 32)) << 32) |
+              (unsigned int)__builtin_amdgcn_readfirstlane((int)q);
+          const int64_t left = total - (int64_t)q;
           const int valid = left >= batch ? batch : left > 0 ? (int)left : 0;
           const int used = min(need - have, valid);
-          if (!act && rank >= have && rank - have < used) g = (int64_t)got + (rank - have);
-          seen = (int64_t)got + batch;
-          stock = (int64_t)got + used;
+          if (!act && rank >= have && rank - have < used) g = (int64_t)q + (rank - have);
+          seen = (int64_t)q + batch;
+          stock = (int64_t)q + used;
           n_stock = valid - used;
           if (need - have > valid) {
             pack = true;
@@ -719,10 +714,10 @@ __global__ __launch_bounds__(LB) void lsrk_persistent(PoolArgs a) {
     const int nw = (B + 63) >> 6;
     if (lane == 0) s_wave_cnt[par][wave] = __popcll(ball);
     __syncthreads();
-    int off = 0, n_active = 0, busy = 0;
+    int before = 0, n_active = 0, busy = 0;
     for (int w = 0; w < nw; ++w) {
       const int cnt = s_wave_cnt[par][w];
-      if (w < wave) off += cnt;
+      if (w < wave) before += cnt;
       n_active += cnt;
       busy += cnt > 0;
     }
@@ -732,7 +727,7 @@ __global__ __launch_bounds__(LB) void lsrk_persistent(PoolArgs a) {
       if (n_active == 0) break;
       if ((n_active + 63) >> 6 == busy) continue;  // no wave would end by it
     }
-    const int rank = off + __popcll(ball & below);
+    const int rank = before + __popcll(ball & below);
     if (act) {
 #pragma unroll
       for (int v = 0; v < N1; ++v) sd[(size_t)v * B + rank] = u[v];
@@ -750,10 +745,10 @@ __global__ __launch_bounds__(LB) void lsrk_persistent(PoolArgs a) {
       const int want = B - n_active;
       const unsigned long long cur = __hip_atomic_load(a.next, __ATOMIC_RELAXED,
                                                        __HIP_MEMORY_SCOPE_AGENT);
-      long long got = 0;
-      if ((int64_t)cur < total) got = (long long)atomicAdd(a.next, (unsigned long long)want);
+      long long q = 0;
+      if ((int64_t)cur < total) q = (long long)atomicAdd(a.next, (unsigned long long)want);
       s_take = (int64_t)cur < total ? want : 0;
-      s_base = got;
+      s_base = q;
     }
     __syncthreads();
     if (tid < n_active) {
@@ -874,13 +869,11 @@ struct MechEntry {
   int train_w4t_ld;
   long train_wt4, train_wt2;
   int tail_rd;  // doubles per tail record carrying the state (TailRec)
+  bool rate_table;  // the LSRK kernels hold the exponentials' table (kRateTable)
 };
 
 // Kernels are instantiated for launch bounds 256 (blocks of 64..256 threads)
-// and 512, and where the rates' table wants it for 64; the bound caps the registers the compiler may give a lane.
-template <class M, int S>
-constexpr int kSmallBlock = M::CONC && S == SCHEME_LSRK ? 64 : 256;
-
+// and 512; the bound caps the registers the compiler may give a lane.
 template <class M, int S>
 hipError_t launch_direct_s(const PoolArgs& a, int block, hipStream_t s) {
   const int64_t grid = (a.one.n + block - 1) / block;
@@ -888,9 +881,7 @@ hipError_t launch_direct_s(const PoolArgs& a, int block, hipStream_t s) {
   if constexpr (S == SCHEME_ROS4) {
     hipLaunchKernelGGL((lsrk_direct<M, 256, S>), dim3((unsigned)grid), dim3(block), 0, s, a);
   } else {
-    if (block == 64)
-      hipLaunchKernelGGL((lsrk_direct<M, kSmallBlock<M, S>, S>), dim3((unsigned)grid), dim3(block), 0, s, a);
-    else if (block <= 256)
+    if (block <= 256)
       hipLaunchKernelGGL((lsrk_direct<M, 256, S>), dim3((unsigned)grid), dim3(block), 0, s, a);
     else
       hipLaunchKernelGGL((lsrk_direct<M, 512, S>), dim3((unsigned)grid), dim3(block), 0, s, a);
@@ -921,10 +912,7 @@ hipError_t launch_persistent_s(const PoolArgs& a, int block, int grid, hipStream
     hipLaunchKernelGGL((lsrk_persistent<M, 256, S>), dim3(grid), dim3(block),
                        Slots<M>::bytes(block), s, a);
   } else {
-    if (block == 64)
-      hipLaunchKernelGGL((lsrk_persistent<M, kSmallBlock<M, S>, S>), dim3(grid), dim3(block),
-                         Slots<M>::bytes(block), s, a);
-    else if (block <= 256)
+    if (block <= 256)
       hipLaunchKernelGGL((lsrk_persistent<M, 256, S>), dim3(grid), dim3(block),
                          Slots<M>::bytes(block), s, a);
     else
@@ -982,10 +970,7 @@ int max_blocks_per_cu_s(int block) {
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, lsrk_persistent<M, 256, S>, block,
                                                      Slots<M>::bytes(block));
   } else {
-    if (block == 64)
-      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb, lsrk_persistent<M, kSmallBlock<M, S>, S>, block, Slots<M>::bytes(block));
-    else if (block <= 256)
+    if (block <= 256)
       e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, lsrk_persistent<M, 256, S>, block,
                                                        Slots<M>::bytes(block));
     else
@@ -1013,7 +998,7 @@ int max_blocks_per_cu(int block, int scheme) {
                        &max_blocks_per_cu<M>, \
                        &launch_surr_infer<M>, &launch_make_pairs<M>, &launch_train<M>, \
                        TrainSizes<M>::wtpack_elems, TrainSizes<M>::w4t_ld, TrainSizes<M>::wt4, \
-                       TrainSizes<M>::wt2, TailRec<M>::RD},
+                       TrainSizes<M>::wt2, TailRec<M>::RD, kRateTable<M, SCHEME_LSRK>},
 const MechEntry g_registry[] = {CHEM_FOR_EACH_MECH(CHEM_ENTRY)};
 #undef CHEM_ENTRY
 
@@ -1265,6 +1250,11 @@ int check_scheme_launch(chem_mech m, const chem_opts* o, int block) {
 }
 
 constexpr int kDefaultBlock = 128;
+// Kernels that hold the exponentials' table run in blocks of 128 where 64 are
+// asked for: beside it, three waves would fit a CU.  Measured (block 64 with the
+// table in LDS, in memory, and as 128; ms): 1 M stiff cells 12.0, 8.7, 8.6,
+// 200,000 cells of one step without a hand-off 0.144, 0.149, 0.081.
+constexpr int kTableBlock = 128;
 constexpr int kDefaultChunk = 8;
 
 int size_bucket(int64_t total) {
@@ -1353,6 +1343,7 @@ Launch pick_launch(chem_mech m, int64_t total, const chem_opts* o) {
     take(it->second.block, it->second.chunk, it->second.tail, o && o->tail_steps ? 0 : it->second.cap,
          it->second.order);
   if (o) take(o->block_size, o->chunk_steps, o->tail_steps, o->tail_cap, o->pool_order);
+  if (m->entry->rate_table && (!o || o->scheme == SCHEME_LSRK)) l.block = std::max(l.block, kTableBlock);
   return l;
 }
 
@@ -1900,7 +1891,7 @@ const char* chem_strerror(int code) {
 const char* chem_last_error(void) { return g_err.c_str(); }
 
 int chem_eval_math(int32_t fn, const double* x, double* y, int64_t n, void* stream) {
-  if (fn < 0 || fn > CHEM_MATH_STEP_FACTOR || fn == 1 || fn == 7)
+  if (fn < 0 || fn > CHEM_MATH_STEP_FACTOR || fn == 1 || fn == 7 || fn == 8)
     return fail(CHEM_EINVAL, "chem_eval_math: unknown function");
   if (n < 0 || (n > 0 && (!x || !y))) return fail(CHEM_EINVAL, "chem_eval_math: bad argument");
   if (n == 0) return CHEM_OK;

@@ -164,11 +164,8 @@ typedef const __attribute__((address_space(3))) double lds_cdouble;
 // slots.  Against the polynomial (both on exponents in base 2, one FMA less): 4.2
 // M stiff cells 22.2 -> 20.8 ms, 96-box hierarchy 8.2 -> 7.6, 65,536 cells x 100
 // calls 8.1 -> 7.5.
-// Blocks of 64 lanes read the table from memory instead (ExpTable<const
-// double*>, the same bits): in LDS it would leave room for three waves per CU.
-template <class P>
 struct ExpTable {
-  P E;
+  lds_cdouble* E;
   __device__ __forceinline__ double operator()(double x) const {
     constexpr double MAGIC = 6755399441055744.0;  // 1.5 2^52
     constexpr double C1 = 0x1.62e42fefa39efp-1, C2 = 0x1.ebfbdff82c58fp-3, C3 = 0x1.c6b08d704a0c0p-5;

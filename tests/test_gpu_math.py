@@ -40,9 +40,8 @@ def exponents(scale, seed):
 # exp_coop the same with 0.03 for the roundings of p (|p| < 2^-7.5, below 4 ulp of
 # p); exp_poly 0.85 for the polynomial and two roundings of f (half an ulp of 1/2
 # each, times ln 2: 0.35 ulp each of a result near 1); exp_ranged is exp_cw.
-@pytest.mark.parametrize("fn,scale,bound", [("exp_table", 4096, 1.03), ("exp_table_mem", 4096, 1.03),
-                                            ("exp_coop", 64, 1.03), ("exp_poly", 1, 1.55),
-                                            ("exp_ranged", 1, 1.0)])
+@pytest.mark.parametrize("fn,scale,bound", [("exp_table", 4096, 1.03), ("exp_coop", 64, 1.03),
+                                            ("exp_poly", 1, 1.55), ("exp_ranged", 1, 1.0)])
 def test_rate_exponentials(cg, fn, scale, bound):
     x = exponents(scale, 51)
     u = ulps(device(cg, fn, x), np.exp(x.astype(np.longdouble)))
@@ -56,11 +55,8 @@ def test_rate_exponentials(cg, fn, scale, bound):
     assert y[0] == 1.0 and (y[1:4] == np.inf).all() and (y[4:7] == 0.0).all() and np.isnan(y[7])
 
 
-def test_bits_shared_by_the_variants(cg):
-    """The table in memory gives the LDS table's bits, the ranged exponential
-    exp_cw's."""
+def test_ranged_exponential_keeps_the_bits(cg):
     x = np.concatenate([exponents(4096, 52), exponents(1, 53)])
-    assert np.array_equal(device(cg, "exp_table", x), device(cg, "exp_table_mem", x))
     assert np.array_equal(device(cg, "exp_ranged", x), device(cg, "exp_cw", x))
 
 
