@@ -77,8 +77,10 @@ __device__ __forceinline__ float dsilu_fast(float z) {
   return s * (1.0f + z * (1.0f - s));
 }
 
-// x mod n; for n below 2^31 (x below 2^62 then) from the FP64 quotient, which
-// is off by at most one, in place of a 64-bit division.
+// x mod n for x <= n^2 (a permutation's multiplier and offset are below n, a
+// batch ends before the second epoch): for n below 2^31 from the FP64 quotient,
+// which is below 2^31 then and off by at most one, in place of a 64-bit
+// division.
 __device__ __forceinline__ unsigned long long mod_n(unsigned long long x, unsigned long long n) {
   if (x < n) return x;
   if (n >= (1ull << 31) || x >= (1ull << 62)) return x % n;
