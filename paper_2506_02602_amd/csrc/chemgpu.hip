@@ -1220,7 +1220,8 @@ int check_capacity(chem_mech m, int64_t cells, const char* where) {
 Control make_control(const chem_opts* o) {
   Control c;
   c.rtol = (o && o->rtol > 0) ? o->rtol : 1e-8;
-  c.atol = (o && o->atol > 0) ? o->atol : 1e-10;
+  // (the norm takes reciprocals of rtol |u| + atol: a normal number at least)
+  c.atol = (o && o->atol > 0) ? std::max(o->atol, 1e-300) : 1e-10;
   c.max_steps = (o && o->max_steps > 0) ? o->max_steps : 100000;
   return c;
 }

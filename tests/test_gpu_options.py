@@ -86,3 +86,25 @@ def test_tuning_keeps_the_direct_launch(mech9_path, n):
         s = np.ascontiguousarray(s0[:, hot][:, :4500])     # 4,097 to 8,192: the same bucket
         assert run()[1]
     gm.close()
+
+
+@pytest.mark.parametrize("opt", [{}, dict(tail_steps=-1), dict(scheme="rkf45")])
+def test_tiny_absolute_tolerance(mech9_path, opt):
+    """An absolute tolerance below the smallest normal number: cells of an inert
+    gas, whose errors are all zero, still take their one step."""
+    import torch
+    from paper_2506_02602_amd import chemgpu as cg
+    names, W = wl.read_species(mech9_path)
+    n = 100
+    Y = np.zeros((len(names), n))
+    Y[names.index("N2")] = 1.0
+    T = np.linspace(400.0, 2500.0, n)
+    s = wl.pack(T, Y, wl.density(T, np.full(n, wl.P_ATM), Y, W))
+    gm = cg.chem_mech_load(mech9_path)
+    cg.chem_workspace_reserve(gm, n)
+    st, status = to_gpu(s), torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    cg.chem_integrate(gm, st, wl.DT_FLOW, cg.make_opts(atol=1e-310, **opt), status=status)
+    torch.cuda.synchronize()
+    assert (status == 0).all()
+    assert np.array_equal(st.cpu().numpy()[:10], s[:10])
+    gm.close()
