@@ -158,7 +158,7 @@ typedef const __attribute__((address_space(3))) double lds_cdouble;
 // 2^((m & 4095)/4096) from LDS (correctly rounded) and p the degree-3 Taylor
 // polynomial of 2^(f/4096) - 1 (truncation below 3e-18), e + e p rounded once:
 // within 1.03 ulp.  The per-lane kernels are bound by VALU issue, and this takes
-// 12 of those instructions and an LDS read where the polynomial takes 17; 30
+// 12 of those instructions and an LDS read where the polynomial takes 17; 29
 // exponentials are in a stage of 9 species.  A smaller table needs a term more
 // (2,048 entries) or two, a larger one does not fit the LDS beside the packing
 // slots.  Against the polynomial (both on exponents in base 2, one FMA less): 4.2

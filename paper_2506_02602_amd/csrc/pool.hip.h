@@ -60,11 +60,12 @@ struct TailBuf {
   unsigned int* btot;     // records per key bucket (zeroed before launch)
   unsigned int* bcur;     // per key bucket: records given a position so far (zeroed)
   unsigned long long* coop_steps;  // steps the cooperative kernel took (zeroed; measurement)
-  int cap;                // at most this many records go to the cooperative kernel; more
-                          // are resumed one per lane (the count decides, so the choice is
-                          // a function of the input only)
-  // auto_coop > 0: and only when it is expected to end first (coop_pays): how
-  // many steps the chip finishes, cooperatively and one cell per lane, in the
+  // The records go to the cooperative kernel when they are at most cap and
+  // (auto_coop > 0) it is expected to end first (coop_pays), else they are
+  // resumed one per lane; count and keys decide, so the choice is a function of
+  // the input only.
+  int cap;
+  // how many steps the chip finishes, cooperatively and one cell per lane, in the
   // time of one step of a lone cooperative group, and the power of a cell's
   // estimate that its steps grow like
   float auto_coop, auto_lane, auto_pow;
