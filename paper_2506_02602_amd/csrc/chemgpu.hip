@@ -175,17 +175,24 @@ __global__ void pool_reset(unsigned long long* next, unsigned int* tail_count,
 // fewer than two steps, up to kTailBuckets - 1.
 constexpr int kTailBuckets = 64;
 
-// rem/h steps for the time rem left in the present sub-call, and in each of
-// the `later` ones the geometric mean of one step and of the dt/h it would
-// take at the present step size: a cell of a step per sub-call may ignite in a
-// later one, and one that steps finely now is often in a transient.  Rank
+// rem/h steps for the time rem = dt - t left in the present sub-call, and in
+// each of the `later` ones the geometric mean of one step and of the dt/h it
+// would take at the present step size: a cell of a step per sub-call may ignite
+// in a later one, and one that steps finely now is often in a transient.  Where
+// every step of the sub-call so far grew by the largest factor, 5 (h >= 4 t), h
+// still stems from the last sub-call's last step, which is cut to end on dt: the
+// cell's steps up to now, `steps` of them, are then taken for its size if they
+// were longer.  (One such row of 256 estimated at up to 14 times its steps sent
+// 65,536 cells x 100 sub-calls to the cooperative kernel: 17.2 ms for 7.8.)  Rank
 // correlation with the steps that the cells then take (hand-off after 4 steps;
 // the present step size to the end instead): 65,536-cell ignition profiles
 // through 100 sub-calls 0.88 and 0.91 (0.77, 0.78), through 30 0.92 and 0.95
 // (0.81, 0.82), hot cells through 4 0.98 (0.98).
-__device__ __forceinline__ double tail_steps_left(double rem, double dt, int later, double h) {
-  const double est = rem / h;
-  return est + (float)later * fmaxf(1.f, __builtin_amdgcn_sqrtf((float)(dt / h)));
+__device__ __forceinline__ double tail_steps_left(double t, double dt, int sub, int n_sub,
+                                                  double h, int steps) {
+  if (h >= 4.0 * t) h = fmax(h, fma((double)sub, dt, t) / (double)steps);
+  const double est = (dt - t) / h;
+  return est + (float)(n_sub - 1 - sub) * fmaxf(1.f, __builtin_amdgcn_sqrtf((float)(dt / h)));
 }
 
 __device__ __forceinline__ int32_t tail_key(double est) {
@@ -235,16 +242,16 @@ __device__ __forceinline__ float resume_priority(const unsigned int* btot, float
 // fields, 0.45 to 0.60 for 32), as the largest estimates are the least certain.
 // Measured (ms; cooperative against per lane, the kernel it takes marked):
 //   cells x sub-calls       16,000      27,000      40,000      50,000      65,536     100,000
-//   hot                 *1.0   2.7  *1.4   3.1  *2.0   3.2  *2.4   3.0   3.1  *3.1   4.6  *3.2
-//   stress              *0.9   2.7  *1.1   2.8  *1.4   2.8  *1.7   2.8  *2.1   2.8   3.0  *2.9
-//   ignition x 100      *5.7   7.4   8.6  *7.5  11.6  *7.5  13.5  *7.6  17.6  *7.6  25.4  *10.4
-//   ignition x 30       *2.1   3.9   3.3  *4.0   4.5  *4.0   5.2  *4.0   6.6  *4.0   9.7  *5.5
-//   scattered x 100     *5.9  12.1  *9.0  12.2 *12.0  12.3  14.1 *12.3  18.0 *12.6  26.3 *13.3
-//   hot x 10            *7.0  22.3 *10.2  22.2 *13.7  23.2  17.0 *23.2 *21.8  24.6  31.7 *24.6
-//   stress x 10         *7.2  23.2  *9.3  25.5 *11.7  26.5 *14.1  25.9 *17.2  25.9 *24.7  26.5
-//   hot, dt/4 x 4       *1.0   2.7  *1.4   3.2  *2.0   3.3  *2.4   3.0  *3.0   3.1  *4.4   3.0
-// and 32 species: 6,000 stress cells *11.8, 24.3; 10,000 *16.1, 24.1; 14,000
-// 21.9, *23.9; 20,000 30.7, *24.1.
+//   hot                 *1.0   2.7  *1.4   3.2  *1.9   3.2  *2.3   3.1  *2.9   3.1   4.4  *3.1
+//   stress              *0.9   2.8  *1.1   2.9  *1.4   2.9  *1.6   2.9  *2.0   2.9  *3.0   3.0
+//   ignition x 100      *5.9   7.9   8.3  *7.6  11.5  *7.7  13.5  *7.7  17.3  *7.8  25.1  *10.8
+//   ignition x 30       *2.1   4.0   3.2  *4.1   4.4  *4.1   5.3  *4.1   6.6  *4.1   9.5  *5.9
+//   scattered x 100     *6.0  12.3  *8.9  12.5 *11.9  12.6 *13.9  12.7  18.0 *12.8  26.1 *14.0
+//   hot x 10            *6.9  23.9 *10.2  22.8 *13.6  24.1 *16.8  24.3  21.7 *24.9  31.5 *24.8
+//   stress x 10         *7.1  24.6  *9.7  25.9 *12.1  26.1 *14.1  25.8 *17.0  26.7  24.6 *28.1
+//   hot, dt/4 x 4       *1.0   2.7  *1.4   3.2  *2.0   3.2  *2.4   3.1  *3.0   3.1  *4.3   3.1
+// and 32 species: 6,000 stress cells *11.8, 23.5; 10,000 *16.1, 23.6; 14,000
+// 21.9, *24.1; 20,000 30.6, *23.8.
 constexpr float kLaneStep = 4.4f;
 
 // Least steps between refills in the resumption, whose cells have tens of
@@ -605,7 +612,7 @@ __global__ __launch_bounds__(LB) void lsrk_persistent(PoolArgs a) {
         const BoxDesc& bd = box_ref(a, bx);
         const int later = bd.n_sub - 1 - sub;
         const float inv_h = __builtin_amdgcn_rcpf((float)h);
-        est = (float)(bd.dt - t) * inv_h;  // (tail_steps_left in floats)
+        est = (float)(bd.dt - t) * inv_h;  // (tail_steps_left of the present h)
         est += (float)later * fmaxf(1.f, __builtin_amdgcn_sqrtf((float)bd.dt * inv_h));
       }
       if (__any(est >= prio)) __builtin_amdgcn_s_setprio(3);
@@ -663,7 +670,7 @@ __global__ __launch_bounds__(LB) void lsrk_persistent(PoolArgs a) {
           a.tail.sub[r] = sub;
           a.tail.base[r] = base;
         }
-        const int key = tail_key(tail_steps_left(bd.dt - t, bd.dt, bd.n_sub - 1 - sub, h));
+        const int key = tail_key(tail_steps_left(t, bd.dt, sub, bd.n_sub, h, nacc + nrej));
         a.tail.key[r] = key;
         atomicAdd(&s_hist[key], 1u);
         item = -1;
@@ -1311,7 +1318,7 @@ Launch size_launch(chem_mech m, int64_t total) {
   l.tail = wide ? 8 : 4;
   l.cap = INT32_MAX;
   l.order = total >= (wide ? int64_t(1) << 17 : int64_t(1) << 21) ? ORDER_RANGE : 0;
-  l.auto_coop = (wide ? 2.3f : 15.f) * m->n_cu;
+  l.auto_coop = (wide ? 2.3f : 18.f) * m->n_cu;
   l.auto_lane = (wide ? 50.f : 75.f) * m->n_cu;
   l.auto_pow = wide ? 0.45f : 0.65f;
   return l;
