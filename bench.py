@@ -110,13 +110,13 @@ def parse():
 # Keyed by a digest of the kernel sources the counters were taken on; any
 # change nulls it (profiles/surrogate_mech9_256cubed.md,
 # profiles/hbm_counters_lsrk_mech9_front1024_stress.md).
-_COUNTED = "aeec6ed79e761165"
+_COUNTED = "4e5724e49c09961c"
 TRAFFIC = {
     "surrogate256_plain": (_COUNTED, {"lsrk_persistent": 3.5406e+09}),
-    "surrogate256_fallback": (_COUNTED, {"lsrk_persistent": 6.7756e+08}),
-    "surrogate256_inference": (_COUNTED, {"surr_infer": 2.9136e+09}),
-    "front": (_COUNTED, {"lsrk_coop": 1.1419e+07}),
-    "stress9": (_COUNTED, {"lsrk_persistent": 3.1863e+09}),
+    "surrogate256_fallback": (_COUNTED, {"lsrk_persistent": 6.7736e+08}),
+    "surrogate256_inference": (_COUNTED, {"surr_infer": 2.9120e+09}),
+    "front": (_COUNTED, {"lsrk_coop": 1.0735e+07}),
+    "stress9": (_COUNTED, {"lsrk_persistent": 3.1858e+09}),
 }
 
 
@@ -148,11 +148,11 @@ def traffic(workload, kernel):
 # masked lanes count too); BF16 MFMA = 512 x SQ_INSTS_VALU_MFMA_MOPS_BF16.
 # Keyed like TRAFFIC; any kernel change nulls it.
 COUNTER_FLOPS = {
-    "surrogate256_plain": (_COUNTED, {"lsrk_persistent": 2.6440e+11}),
-    "surrogate256_fallback": (_COUNTED, {"lsrk_persistent": 1.5255e+11}),
+    "surrogate256_plain": (_COUNTED, {"lsrk_persistent": 2.6441e+11}),
+    "surrogate256_fallback": (_COUNTED, {"lsrk_persistent": 1.5257e+11}),
     "surrogate256_inference": (_COUNTED, {"surr_infer": 1.3057e+12}),
-    "front": (_COUNTED, {"lsrk_coop": 2.2054e+10}),
-    "stress9": (_COUNTED, {"lsrk_persistent": 8.6879e+11}),
+    "front": (_COUNTED, {"lsrk_coop": 2.2061e+10}),
+    "stress9": (_COUNTED, {"lsrk_persistent": 8.6888e+11}),
 }
 
 
